@@ -9,6 +9,11 @@
 //            read the same buffer) -> series launches per n
 //   per-item fixed-order compensated reduction
 //
+// FP64 items run on the subset tree instead (gbs_host.cpp), grouped by n: each
+// branch runs its groups one after another, roots, levels and subtrees, and then
+// folds the groups' records into their items' results.  Tiles are left to
+// FP32-compensated items and to pairs with a lane grid set by gbs_set_layout.
+//
 // Tiles within a launch are ordered largest first, so the device counter
 // hands out long work first (longest-processing-time schedule).
 
@@ -32,6 +37,7 @@ namespace {
 
 constexpr int kSeriesPerThread = 8;                   // most subsets per lane in the series kernel
 constexpr int kPersistentWaves = 256 * 8;             // wavefronts of the small-item launch
+constexpr size_t kBatchTreeBudget = (size_t)1 << 30;  // entry store of one branch
 
 }  // namespace
 
@@ -39,6 +45,7 @@ struct gbs_plan {
     int device = 0;
     BatchSchedule S;
     double tune_ms = 0.0;
+    int tree_launches = 0;  // kernel launches of the subset-tree groups
     size_t bytes = 0;
     BatchDev d;
     double2* staging = nullptr;  // packed input copy (the graph reads a fixed address)
@@ -66,6 +73,9 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
     const int64_t vbytes = fp32 ? (int64_t)sizeof(float2) : (int64_t)sizeof(double2);
     const int nitems = S.count;
 
+    bool route[gbs::kMaxPairs + 1];  // items of n pairs run on the subset tree
+    for (int n = 0; n <= gbs::kMaxPairs; ++n) route[n] = tree_route(c, n, fp32);
+
     // items (flop yardstick per dimension computed once)
     double flops_of[GBS_MAX_DIM + 1];
     bool have_flops[GBS_MAX_DIM + 1] = {};
@@ -77,11 +87,13 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
         const int N = dims[i], Np = N + (N & 1);
         S.npair[i] = Np / 2;
         S.in_off[i] = S.in_elems;
-        S.a0_off[i] = S.a0_elems;
+        S.a0_off[i] = route[Np / 2] ? -1 : S.a0_elems;
         S.d_off[i] = S.d_elems;
         S.in_elems += (int64_t)N * N;
-        S.a0_elems += (int64_t)Np * Np;
-        S.d_elems += Np;
+        if (!route[Np / 2]) {
+            S.a0_elems += (int64_t)Np * Np;
+            S.d_elems += Np;
+        }
         S.max_n = std::max(S.max_n, Np / 2);
         S.subset_terms += (int64_t)1 << (Np / 2);
         if (!have_flops[N]) {
@@ -103,8 +115,14 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
     int small_pairs = gbs::kSmallPairs;
     if (const char* e = std::getenv("GBS_SMALL_PAIRS")) small_pairs = std::max(0, std::min(gbs::kSmallPairs, atoi(e)));
     std::vector<HostTile> ht;
+    std::vector<int> by_pairs[gbs::kMaxPairs + 1];  // items on the subset tree
     for (int i = 0; i < nitems; ++i) {
         const int n = S.npair[i];
+        if (route[n]) {
+            by_pairs[n].push_back(i);
+            continue;
+        }
+        S.tiled = true;
         if (!fp32 && n >= 1 && n <= small_pairs) {
             S.small.push_back(i);
             continue;
@@ -128,6 +146,28 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
                 ht.push_back(h);
             }
         }
+    }
+    // groups of equal n, most work first, over the branches in turn
+    for (int n = gbs::kMaxPairs; n >= 1; --n) {
+        if (by_pairs[n].empty()) continue;
+        TreeGroup g;
+        g.begin = (int)S.tlist.size();
+        g.count = (int)by_pairs[n].size();
+        S.tlist.insert(S.tlist.end(), by_pairs[n].begin(), by_pairs[n].end());
+        tree_sched(n, (uint64_t)g.count, kBatchTreeBudget, g.S);
+        S.tree.push_back(g);
+    }
+    std::stable_sort(S.tree.begin(), S.tree.end(), [](const TreeGroup& a, const TreeGroup& b) {
+        return (double)a.count * std::ldexp((double)(a.S.n * a.S.n), a.S.n) >
+               (double)b.count * std::ldexp((double)(b.S.n * b.S.n), b.S.n);
+    });
+    for (size_t k = 0; k < S.tree.size(); ++k) {
+        TreeGroup& g = S.tree[k];
+        g.branch = (int)(k % kBatchBranches);
+        g.rec = S.tree_records;
+        S.tree_records += (int64_t)g.count * (int64_t)g.S.records_per_item;
+        S.tree_arena[g.branch] = std::max(S.tree_arena[g.branch], g.S.arena_bytes);
+        if (g.S.fold > 1) S.tree_nodes[g.branch] = std::max(S.tree_nodes[g.branch], g.S.sub);
     }
     {  // largest n first, stable: a counting sort over n = 1..small_pairs
         std::vector<int> by_n[gbs::kSmallPairs + 1];
@@ -220,14 +260,42 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
 }
 
 gbs_status batch_enqueue(DevCtx* c, const BatchSchedule& S, const BatchDev& d, hipStream_t cs, hipStream_t* br,
-                         const std::function<hipError_t(hipEvent_t*)>& new_event, bool prof) {
+                         const std::function<hipError_t(hipEvent_t*)>& new_event, bool prof, int* tree_launches) {
     (void)c;
     const int nitems = S.count;
-    HIP_TRY(gbs::launch_fill_u32(d.counters, (int)std::max<size_t>(1, S.cp.size()), cs));
-    HIP_TRY(gbs::launch_batch_prep(d.mats, d.in_off, d.dims, d.items, nitems, cs));
+    if (S.tiled) {
+        HIP_TRY(gbs::launch_fill_u32(d.counters, (int)std::max<size_t>(1, S.cp.size()), cs));
+        HIP_TRY(gbs::launch_batch_prep(d.mats, d.in_off, d.dims, d.items, nitems, cs));
+    }
+    std::vector<hipEvent_t> tree_joins;
     hipEvent_t ev_prep;
     HIP_TRY(new_event(&ev_prep));
     HIP_TRY(hipEventRecord(ev_prep, cs));
+    // subset-tree groups: one after another on their branch
+    for (int b = 0; b < kBatchBranches; ++b) {
+        bool first = true;
+        for (const TreeGroup& g : S.tree) {
+            if (g.branch != b) continue;
+            if (first) HIP_TRY(hipStreamWaitEvent(br[b], ev_prep, 0));
+            first = false;
+            TreeBufs tb;
+            tb.arena = d.tarena[b];
+            tb.nodes = d.tnodes[b];
+            double* rec = d.trec + 5 * g.rec;
+            const gbs_status e = tree_enqueue(g.S, tb, gbs::TreeSource{d.mats, d.in_off, d.dims, d.tlist + g.begin, 0},
+                                              nullptr, rec, br[b], tree_launches, prof);
+            if (e != GBS_OK) return e;
+            HIP_TRY(gbs::launch_tree_items(d.tlist + g.begin, g.count, rec, (int64_t)g.S.records_per_item, d.out, d.abs,
+                                           br[b]));
+            if (tree_launches) ++*tree_launches;
+        }
+        if (!first) {
+            hipEvent_t ej;
+            HIP_TRY(new_event(&ej));
+            HIP_TRY(hipEventRecord(ej, br[b]));
+            tree_joins.push_back(ej);
+        }
+    }
     hipEvent_t ev_small = nullptr;
     if (!S.small.empty()) {
         hipStream_t bs = br[kBatchBranches - 1];
@@ -273,7 +341,8 @@ gbs_status batch_enqueue(DevCtx* c, const BatchSchedule& S, const BatchDev& d, h
         HIP_TRY(hipEventRecord(ev_series[r], cs));
     }
     if (ev_small) HIP_TRY(hipStreamWaitEvent(cs, ev_small, 0));
-    HIP_TRY(gbs::launch_item_reduce(d.pbeg, nitems, d.partials, d.items, d.out, d.abs, cs));
+    for (hipEvent_t ej : tree_joins) HIP_TRY(hipStreamWaitEvent(cs, ej, 0));
+    if (S.tiled) HIP_TRY(gbs::launch_item_reduce(d.pbeg, nitems, d.partials, d.items, d.out, d.abs, cs));
     return GBS_OK;
 }
 
@@ -316,13 +385,20 @@ void plan_free(gbs_plan* p) {
                     d.abs,      d.small,    const_cast<uint64_t*>(d.binom), const_cast<int4*>(d.lbmap)};
     for (void* b : bufs)
         if (b) hipFree(b);
+    for (int b = 0; b < kBatchBranches; ++b) {
+        if (d.tarena[b]) hipFree(d.tarena[b]);
+        if (d.tnodes[b]) hipFree(d.tnodes[b]);
+    }
+    if (d.tlist) hipFree(d.tlist);
+    if (d.trec) hipFree(d.trec);
     delete p;
 }
 
 std::vector<gbs::BatchItem> item_table(const BatchSchedule& S, double2* a0, double2* dv) {
     std::vector<gbs::BatchItem> items(S.count);
     for (int i = 0; i < S.count; ++i)
-        items[i] = gbs::BatchItem{a0 + S.a0_off[i], dv + S.d_off[i], 2 * S.npair[i], S.npair[i]};
+        items[i] = gbs::BatchItem{S.a0_off[i] < 0 ? nullptr : a0 + S.a0_off[i], dv + S.d_off[i], 2 * S.npair[i],
+                                  S.npair[i]};
     return items;
 }
 
@@ -348,6 +424,12 @@ gbs_status plan_build_into(DevCtx* c, const std::vector<int>& dims, bool fp32, i
     if ((st = upload(&d.sblocks, S.sblocks, &B)) != GBS_OK) return st;
     if ((st = upload(&d.pbeg, S.pbeg, &B)) != GBS_OK) return st;
     if ((st = upload(&d.small, S.small, &B)) != GBS_OK) return st;
+    if ((st = upload(&d.tlist, S.tlist, &B)) != GBS_OK) return st;
+    for (int b = 0; b < kBatchBranches; ++b) {
+        if ((st = dmalloc(&d.tarena[b], S.tree_arena[b], &B)) != GBS_OK) return st;
+        if ((st = dmalloc((void**)&d.tnodes[b], 40 * (size_t)S.tree_nodes[b], &B)) != GBS_OK) return st;
+    }
+    if ((st = dmalloc((void**)&d.trec, 40 * (size_t)S.tree_records, &B)) != GBS_OK) return st;
     {  // the plan's own copies of the context's tables: a plan outlives gbs_finalize
         void* tb = nullptr;
         const size_t nb = sizeof(uint64_t) * gbs::kBinomStride * gbs::kBinomStride;
@@ -381,7 +463,7 @@ gbs_status plan_build_into(DevCtx* c, const std::vector<int>& dims, bool fp32, i
         return r;
     };
     HIP_TRY(hipStreamBeginCapture(p->cs, hipStreamCaptureModeThreadLocal));
-    if ((st = batch_enqueue(c, S, d, p->cs, p->br, new_event, false)) != GBS_OK) return st;
+    if ((st = batch_enqueue(c, S, d, p->cs, p->br, new_event, false, &p->tree_launches)) != GBS_OK) return st;
     HIP_TRY(hipStreamEndCapture(p->cs, &p->graph));
     HIP_TRY(hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0));
     return GBS_OK;
@@ -421,6 +503,8 @@ struct gbs_host::BatchRunner {
     size_t host_meta_cap = 0;
     void* meta = nullptr;
     size_t meta_cap = 0;
+    void *tarena[kBatchBranches] = {}, *tnodes[kBatchBranches] = {}, *trec = nullptr;
+    size_t tarena_cap[kBatchBranches] = {}, tnodes_cap[kBatchBranches] = {}, trec_cap = 0;
     void *a0 = nullptr, *dv = nullptr, *partials = nullptr, *counters = nullptr, *out = nullptr, *abs = nullptr;
     size_t a0_cap = 0, dv_cap = 0, partials_cap = 0, counters_cap = 0, out_cap = 0, abs_cap = 0;
     void* ebuf[2] = {nullptr, nullptr};
@@ -450,6 +534,11 @@ void runner_free(BatchRunner* r) {
     void* bufs[] = {r->meta, r->a0, r->dv, r->partials, r->counters, r->out, r->abs, r->ebuf[0], r->ebuf[1]};
     for (void* b : bufs)
         if (b) hipFree(b);
+    for (void* b : r->tarena)
+        if (b) hipFree(b);
+    for (void* b : r->tnodes)
+        if (b) hipFree(b);
+    if (r->trec) hipFree(r->trec);
     delete r;
 }
 
@@ -464,12 +553,15 @@ gbs_status runner_run(BatchRunner* r, const BatchSchedule& S, const double2* mat
     const size_t n_items = sizeof(gbs::BatchItem) * S.count, n_inoff = sizeof(int64_t) * S.in_off.size(),
                  n_dims = sizeof(int) * S.dims.size(), n_tiles = sizeof(gbs::BatchTile) * S.tiles.size(),
                  n_sb = sizeof(gbs::SeriesBlock) * S.sblocks.size(), n_pbeg = sizeof(int64_t) * S.pbeg.size(),
-                 n_small = sizeof(int) * S.small.size();
+                 n_small = sizeof(int) * S.small.size(), n_tlist = sizeof(int) * S.tlist.size();
     const size_t o_items = 0, o_inoff = align(o_items + n_items), o_dims = align(o_inoff + n_inoff),
                  o_tiles = align(o_dims + n_dims), o_sb = align(o_tiles + n_tiles), o_pbeg = align(o_sb + n_sb),
-                 o_small = align(o_pbeg + n_pbeg), total = align(o_small + n_small);
+                 o_small = align(o_pbeg + n_pbeg), o_tlist = align(o_small + n_small), total = align(o_tlist + n_tlist);
     const size_t npart = 5 * (size_t)std::max<int64_t>(1, S.pbeg[S.count]);
-    const bool grow = r->meta_cap < total || r->a0_cap < sizeof(double2) * (size_t)S.a0_elems ||
+    bool tree_grow = r->trec_cap < 40 * (size_t)S.tree_records;
+    for (int b = 0; b < kBatchBranches; ++b)
+        tree_grow = tree_grow || r->tarena_cap[b] < S.tree_arena[b] || r->tnodes_cap[b] < 40 * (size_t)S.tree_nodes[b];
+    const bool grow = tree_grow || r->meta_cap < total || r->a0_cap < sizeof(double2) * (size_t)S.a0_elems ||
                       r->dv_cap < sizeof(double2) * (size_t)S.d_elems || r->partials_cap < sizeof(double) * npart ||
                       r->counters_cap < sizeof(unsigned) * std::max<size_t>(1, S.cp.size()) ||
                       r->out_cap < sizeof(double2) * S.count || r->abs_cap < sizeof(double) * S.count ||
@@ -489,6 +581,11 @@ gbs_status runner_run(BatchRunner* r, const BatchSchedule& S, const double2* mat
             return e;
         if ((e = ensure_buffer(&r->out, &r->out_cap, sizeof(double2) * S.count, 1)) != GBS_OK) return e;
         if ((e = ensure_buffer(&r->abs, &r->abs_cap, sizeof(double) * S.count, 1)) != GBS_OK) return e;
+        if ((e = ensure_buffer(&r->trec, &r->trec_cap, 40 * (size_t)S.tree_records, 1)) != GBS_OK) return e;
+        for (int b = 0; b < kBatchBranches; ++b) {
+            if ((e = ensure_buffer(&r->tarena[b], &r->tarena_cap[b], S.tree_arena[b], 1)) != GBS_OK) return e;
+            if ((e = ensure_buffer(&r->tnodes[b], &r->tnodes_cap[b], 40 * (size_t)S.tree_nodes[b], 1)) != GBS_OK) return e;
+        }
         for (int b = 0; b < 2 && b < S.rounds; ++b)
             if ((e = ensure_buffer(&r->ebuf[b], &r->ebuf_cap[b], (size_t)S.ebuf_bytes, 1)) != GBS_OK) return e;
     }
@@ -508,6 +605,7 @@ gbs_status runner_run(BatchRunner* r, const BatchSchedule& S, const double2* mat
     if (n_sb) std::memcpy(h + o_sb, S.sblocks.data(), n_sb);
     std::memcpy(h + o_pbeg, S.pbeg.data(), n_pbeg);
     if (n_small) std::memcpy(h + o_small, S.small.data(), n_small);
+    if (n_tlist) std::memcpy(h + o_tlist, S.tlist.data(), n_tlist);
     HIP_TRY(hipMemcpyAsync(r->meta, h, total, hipMemcpyHostToDevice, st));
     HIP_TRY(hipEventRecord(r->upload_done, st));
     r->uploaded = true;
@@ -524,6 +622,12 @@ gbs_status runner_run(BatchRunner* r, const BatchSchedule& S, const double2* mat
     d.sblocks = (gbs::SeriesBlock*)(m + o_sb);
     d.pbeg = (int64_t*)(m + o_pbeg);
     d.small = (int*)(m + o_small);
+    d.tlist = (int*)(m + o_tlist);
+    for (int b = 0; b < kBatchBranches; ++b) {
+        d.tarena[b] = r->tarena[b];
+        d.tnodes[b] = (double*)r->tnodes[b];
+    }
+    d.trec = (double*)r->trec;
     d.partials = (double*)r->partials;
     d.counters = (unsigned*)r->counters;
     d.ebuf[0] = r->ebuf[0];
@@ -557,7 +661,11 @@ gbs_status runner_run(BatchRunner* r, const BatchSchedule& S, const double2* mat
 
 namespace {
 
-int kernel_nodes_of(const gbs_plan* p) { return 3 + (int)p->S.cp.size() + (int)p->S.se.size(); }
+// Kernel launches of a run: the tile schedule's, and per subset-tree group
+// those of its pieces.
+int kernel_nodes_of(const gbs_plan* p) {
+    return (p->S.tiled ? 3 + (int)p->S.cp.size() + (int)p->S.se.size() : 0) + p->tree_launches;
+}
 
 gbs_status plan_run(gbs_plan* p, const gbs_z* mats_dev, gbs_z* out_dev, double* abs_dev, hipStream_t s,
                     bool prof = false) {
@@ -618,7 +726,9 @@ gbs_status gbs_batch_plan_create(const int32_t* dims, int32_t count, gbs_precisi
         const int n = (N + 1) / 2;
         if (n >= 1 && !seen[n]) {
             seen[n] = true;
-            st = (flags & GBS_PLAN_AUTOTUNE) ? autotune_impl(c, n, nullptr) : maybe_tune(c, n);
+            // items on the subset tree have no lane grid to choose
+            st = ((flags & GBS_PLAN_AUTOTUNE) && !tree_route(c, n, prec == GBS_FP32_COMP)) ? autotune_impl(c, n, nullptr)
+                                                                                           : maybe_tune(c, n);
             if (st != GBS_OK) return st;
         }
     }
@@ -686,6 +796,7 @@ gbs_status gbs_batch_plan_create(const int32_t* dims, int32_t count, gbs_precisi
             if (best) plan_free(best);
             best = p;
             best_ms = ms;
+            if (p->S.tiles.empty()) break;  // nothing depends on the tile size
         } else {
             plan_free(p);
             break;

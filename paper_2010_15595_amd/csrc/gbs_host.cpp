@@ -383,14 +383,247 @@ RankRange shard_ranks(uint64_t cnt, int g, int G) {
     return RankRange{cnt * (uint64_t)g / (uint64_t)G, cnt * (uint64_t)(g + 1) / (uint64_t)G};
 }
 
+// ---- subset tree: a forest of equal trees is expanded level by level from its
+// roots, the lowest levels in pieces that fit the entry store, and every piece's
+// nodes with tree_depth(n) pairs left are finished by launch_tree_sub.
+
+namespace {
+
+// Parents of each level expanded by one launch, and the entries that takes.
+// Below `full` every level is expanded whole; from there on in pieces that
+// feed `sub` nodes to one launch of the subtree kernel.
+uint64_t piece_entries(TreeSched& S, int full, uint64_t sub) {
+    const int L = S.levels;
+    uint64_t e = S.roots * (uint64_t)gbs::tree_entries(S.n);
+    S.off[0] = 0;
+    for (int lv = 0; lv < L; ++lv) {
+        const uint64_t whole = S.roots << lv;
+        const int sh = L - lv;
+        S.piece[lv] = lv < full ? whole : std::min<uint64_t>(whole, std::max<uint64_t>(1, sh < 63 ? sub >> sh : 0));
+        S.off[lv + 1] = e;
+        e += S.piece[lv] * (uint64_t)gbs::tree_entries(S.n - lv - 1);
+    }
+    return e;
+}
+
+}  // namespace
+
+bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records) {
+    S = TreeSched();
+    S.n = n;
+    S.items = items;
+    S.levels = n - gbs::tree_depth(n);
+    const size_t entry = 16 * (size_t)(n + 1);
+    const uint64_t most = budget / entry;
+    // roots in flight: all their levels when they fit
+    uint64_t per = gbs::tree_entries(n);
+    for (int lv = 0; lv < S.levels; ++lv) per += (uint64_t)gbs::tree_entries(n - lv - 1) << lv;
+    S.roots = std::max<uint64_t>(1, std::min<uint64_t>(items, most / per));
+    uint64_t sub = S.roots << S.levels;
+    if (piece_entries(S, S.levels, sub) > most) {
+        uint64_t p2 = 1;
+        while (p2 * 2 <= sub) p2 *= 2;
+        sub = p2;
+        while (sub > 1 && piece_entries(S, 0, sub) > most - most / 4) sub /= 2;
+        if (piece_entries(S, 0, sub) > most) return false;
+        int full = 0;
+        while (full < S.levels && piece_entries(S, full + 1, sub) <= most) ++full;
+        S.entries = piece_entries(S, full, sub);
+    } else {
+        S.entries = piece_entries(S, S.levels, sub);
+    }
+    S.sub = S.levels ? 2 * S.piece[S.levels - 1] : S.roots;
+    S.arena_bytes = S.entries * entry;
+    const uint64_t nodes = 1ull << S.levels;  // per tree
+    if (S.levels > 10) {
+        // records of one launch folded in groups that lie within one tree (a launch's
+        // nodes are whole trees or an aligned power of two of one tree)
+        S.fold = std::min<uint64_t>(1024, S.roots > 1 ? nodes : S.sub);
+        if (S.fold > 1) S.records_per_item = nodes / S.fold;
+        if (items == 1 && S.records_per_item > mid_records) {
+            S.mid = mid_records;
+            S.records_per_item /= mid_records;
+        }
+    }
+    if (S.fold <= 1) {
+        S.fold = 1;
+        S.records_per_item = nodes;
+    }
+    return true;
+}
+
+gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSource& src, const gbs::TreeShard* shard,
+                        double* records, hipStream_t st, int* launches, bool prof) {
+    gbs::TreeMap mp{};
+    mp.arena = static_cast<double2*>(b.arena);
+    mp.n = S.n;
+    for (int lv = 0; lv <= S.levels; ++lv) mp.off[lv] = S.off[lv] * (uint64_t)(S.n + 1);
+    gbs::TreeShard none{};
+    const gbs::TreeShard& sh = shard ? *shard : none;
+    const double flops = gbs_yardstick_flops(2 * S.n) / (double)(1ull << S.levels);
+    const double subsets = (double)(1ull << (S.n - S.levels));
+    const std::string elim = "tree_elim_kernel<" + std::to_string(S.n) + ">",
+                      sub = "tree_sub_kernel<" + std::to_string(S.n) + ">";
+    int nl = 0;
+    auto timed = [&](double f, double c, const std::string& name, const std::function<hipError_t()>& launch) {
+        ++nl;
+        return (prof && profiling_on()) ? prof_charpoly_launch(f, c, st, launch, name) : launch();
+    };
+    uint64_t mid = 0, done = 0;  // folded records held in b.mid, records written
+    for (uint64_t r0 = 0; r0 < S.items; r0 += S.roots) {
+        const uint64_t roots = std::min(S.roots, S.items - r0);
+        for (uint64_t& w : mp.win) w = 0;
+        HIP_TRY(gbs::launch_tree_root(mp, src, r0, roots, st));
+        ++nl;
+        // nodes [g0, g0 + count) of level lv, their entries in place
+        std::function<gbs_status(int, uint64_t, uint64_t)> run = [&](int lv, uint64_t g0, uint64_t count) -> gbs_status {
+            if (lv == S.levels) {
+                double* rec = (S.fold > 1) ? b.nodes : records + 5 * ((r0 << lv) + g0);
+                HIP_TRY(timed(flops * (double)count, subsets * (double)count, sub,
+                              [&] { return gbs::launch_tree_sub(mp, sh, lv, g0, count, rec, st); }));
+                if (S.fold == 1) return GBS_OK;
+                const uint64_t out = count / S.fold;
+                HIP_TRY(gbs::launch_records_fold(b.nodes, (int64_t)count, (int64_t)S.fold,
+                                                 S.mid ? b.mid + 5 * mid : records + 5 * done, st));
+                ++nl;
+                if (!S.mid) {
+                    done += out;
+                    return GBS_OK;
+                }
+                mid += out;
+                if (mid == S.mid) {
+                    HIP_TRY(gbs::launch_records_fold(b.mid, (int64_t)mid, (int64_t)mid, records + 5 * done, st));
+                    ++nl;
+                    mid = 0;
+                    ++done;
+                }
+                return GBS_OK;
+            }
+            for (uint64_t q = 0; q < count; q += S.piece[lv]) {
+                const uint64_t len = std::min(S.piece[lv], count - q);
+                mp.win[lv + 1] = g0 + q;
+                HIP_TRY(timed(0.0, 0.0, elim, [&] { return gbs::launch_tree_elim(mp, sh, lv, g0 + q, len, st); }));
+                const gbs_status e = run(lv + 1, 2 * (g0 + q), 2 * len);
+                if (e != GBS_OK) return e;
+            }
+            return GBS_OK;
+        };
+        const gbs_status e = run(0, 0, roots);
+        if (e != GBS_OK) return e;
+    }
+    if (launches) *launches += nl;
+    return GBS_OK;
+}
+
+// Mask of the s-subset of {0..n-1} with colexicographic rank `rank`.
+static uint64_t colex_mask(uint64_t rank, int n, int s) {
+    uint64_t mask = 0;
+    for (int c = n - 1, i = s; i >= 1; --i, --c) {
+        while (binom_host(c, i) > rank) --c;
+        mask |= 1ull << c;
+        rank -= binom_host(c, i);
+    }
+    return mask;
+}
+
+gbs::TreeShard tree_shard(int n, int shard, int nshards) {
+    gbs::TreeShard sh{};
+    sh.on = nshards > 1;
+    for (int s = 1; s <= n && sh.on; ++s) {
+        const uint64_t cnt = binom_host(n, s);
+        const uint64_t lo = cnt * (uint64_t)shard / (uint64_t)nshards, hi = cnt * (uint64_t)(shard + 1) / (uint64_t)nshards;
+        if (lo >= hi) continue;  // lo = hi = 0: none
+        // colex order of equal-size subsets is the order of their masks
+        sh.lo[s] = colex_mask(lo, n, s);
+        sh.hi[s] = hi == cnt ? 1ull << n : colex_mask(hi, n, s);
+    }
+    return sh;
+}
+
+// Masks of {0..2^n - 1} below `m` with c set bits.
+static uint64_t masks_below(uint64_t m, int n, int c) {
+    uint64_t r = 0;
+    int left = c;
+    if (m >> n) return binom_host(n, c);
+    for (int b = n - 1; b >= 0 && left >= 0; --b)
+        if ((m >> b) & 1ull) {
+            r += binom_host(b, left);  // this bit 0, the rest free
+            --left;
+        }
+    return r;  // (m itself is not below m)
+}
+
+double tree_shard_share(const gbs::TreeShard& sh, int n) {
+    // nodes with T pairs left (prefixes p of n - T bits) that hold a subset of the
+    // shard: between two consecutive interval ends the same classes are open
+    const int T = gbs::tree_depth(n), L = n - T;
+    std::vector<uint64_t> cut{0, 1ull << L};
+    for (int s = 1; s <= n; ++s)
+        if (sh.lo[s] < sh.hi[s]) {
+            cut.push_back(sh.lo[s] >> T);
+            cut.push_back(((sh.hi[s] - 1) >> T) + 1);
+        }
+    std::sort(cut.begin(), cut.end());
+    double active = 0.0;
+    for (size_t i = 0; i + 1 < cut.size(); ++i) {
+        const uint64_t a = cut[i], b = cut[i + 1];
+        if (a == b) continue;
+        for (int pc = 0; pc <= L; ++pc) {
+            bool open = false;
+            for (int s = std::max(1, pc); s <= pc + T; ++s)
+                open = open || (sh.lo[s] < sh.hi[s] && (sh.lo[s] >> T) <= a && ((sh.hi[s] - 1) >> T) + 1 >= b);
+            if (open) active += (double)(masks_below(b, L, pc) - masks_below(a, L, pc));
+        }
+    }
+    return active / (double)(1ull << L);
+}
+
+// Subset sum on the subset tree: matrix A (device, N x N); shard g of G and
+// record_dev as for run_sum.
+constexpr size_t kTreeBudget = (size_t)4 << 30;  // entry stores of a single evaluation
+gbs_status run_sum_tree(DevCtx* c, const double2* A, int N, hipStream_t st, double2* out_dev, double* abs_dev,
+                        int* launches, int shard, int nshards, double* record_dev) {
+    const int n = (N + 1) / 2;
+    TreeSched S;
+    if (!tree_sched(n, 1, kTreeBudget, S)) return fail(GBS_E_TOO_LARGE, "no subset-tree schedule for %d pairs", n);
+    gbs_status s1 = ensure_buffer(&c->E, &c->E_cap, S.arena_bytes, 1);
+    if (s1 != GBS_OK) return s1;
+    const size_t nrec = S.records_per_item + (S.fold > 1 ? S.sub : 0) + S.mid;
+    s1 = ensure_buffer((void**)&c->partials, &c->partials_cap, nrec * 5, sizeof(double));
+    if (s1 != GBS_OK) return s1;
+    TreeBufs b;
+    b.arena = c->E;
+    b.nodes = c->partials + 5 * S.records_per_item;
+    b.mid = b.nodes + 5 * (S.fold > 1 ? S.sub : 0);
+    const gbs::TreeShard sh = tree_shard(n, shard, nshards);
+    int nl = 0;
+    s1 = tree_enqueue(S, b, gbs::TreeSource{A, nullptr, nullptr, nullptr, N}, sh.on ? &sh : nullptr, c->partials, st, &nl,
+                      true);
+    if (s1 != GBS_OK) return s1;
+    const int64_t np = (int64_t)S.records_per_item;
+    HIP_TRY(timed_launch(kProfReduce, 0.0, 0.0, st, [&] {
+        return record_dev ? gbs::launch_partials_fold(c->partials, np, record_dev, st)
+                          : gbs::launch_final_reduce(c->partials, np, out_dev, abs_dev, st);
+    }));
+    if (launches) *launches = nl + 1;
+    return GBS_OK;
+}
+
+// A shard's ranks of the size classes are scattered over the subset tree, so the
+// nodes that hold any of its subsets are share * G times its share of the
+// subsets (1.3 for two shards, 1.9 to 3.3 for the outer and middle ones of
+// eight, 6 and more for the middle ones of sixteen and up, at n = 24), while the
+// register-tile kernels do just its subsets, each at several times the cost.
+constexpr double kTreeShardCost = 3.4;
+
 // lds_method >= 0 selects the LDS-resident kernels with that characteristic-polynomial method.
 // Shard g of G (FP64 / FP32 paths only) sums its ranks of every class; with
 // record_dev set, the compensated partial (sum, compensation re / im, sum |t|)
 // is written there instead of the rounded result.
-gbs_status run_sum(DevCtx* c, int Np, hipStream_t st, double2* out_dev, double* abs_dev, int* launches,
-                   gbs_precision prec, double2* lo_dev = nullptr, int lds_method = -1, int shard = 0,
+gbs_status run_sum(DevCtx* c, const double2* A, int N, hipStream_t st, double2* out_dev, double* abs_dev,
+                   int* launches, gbs_precision prec, double2* lo_dev = nullptr, int lds_method = -1, int shard = 0,
                    int nshards = 1, double* record_dev = nullptr) {
-    const int n = Np / 2;
+    const int Np = N + (N & 1), n = Np / 2;
     int nl = 0;
     if (n == 0) {  // the empty matrix: one term, 1, in shard 0
         const double one = (shard == 0) ? 1.0 : 0.0;
@@ -406,11 +639,16 @@ gbs_status run_sum(DevCtx* c, int Np, hipStream_t st, double2* out_dev, double* 
         if (launches) *launches = 1;
         return GBS_OK;
     }
+    bool tree = prec == GBS_FP64 && lds_method < 0 && tree_route(c, n, false);
+    if (tree && nshards > 1)
+        tree = tree_shard_share(tree_shard(n, shard, nshards), n) * nshards <= kTreeShardCost;
+    if (!tree) HIP_TRY(gbs::launch_prep(A, N, N, Np, c->A0, c->dvec, st));
     if (prec == GBS_DD || lds_method >= 0)
         return run_sum_lds(c, Np, st, out_dev, lo_dev, abs_dev, launches, prec == GBS_DD ? 1 : 0,
                            lds_method >= 0 ? lds_method : gbs::kCharpolyLaBudde);
     if (lo_dev) HIP_TRY(gbs::launch_scalar_set(lo_dev, make_double2(0.0, 0.0), nullptr, 0.0, st));
     const bool fp32 = prec == GBS_FP32_COMP;
+    if (tree) return run_sum_tree(c, A, N, st, out_dev, abs_dev, launches, shard, nshards, record_dev);
     const int D = n + 1;
     uint64_t max_len = 0, total_blocks = 0, total_len = 0;
     bool one_launch = true;  // every size class in one launch on the register-tile kernels
@@ -520,9 +758,8 @@ gbs_status lhaf_host_matrix(const gbs_z* A, int32_t N, gbs_z* out, gbs_diag* dia
     HIP_TRY(hipStreamWaitEvent(c->stream, c->done, 0));
     if (N > 0) HIP_TRY(hipMemcpyAsync(c->Ain, A, sizeof(gbs_z) * (size_t)N * N, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipEventRecord(c->t0, c->stream));
-    if (Np > 0) HIP_TRY(gbs::launch_prep(c->Ain, N, N, Np, c->A0, c->dvec, c->stream));
     int launches = 0;
-    st = run_sum(c, Np, c->stream, c->res, reinterpret_cast<double*>(c->res + 1), &launches, prec, c->res + 2,
+    st = run_sum(c, c->Ain, N, c->stream, c->res, reinterpret_cast<double*>(c->res + 1), &launches, prec, c->res + 2,
                  lds_method);
     if (st != GBS_OK) return st;
     HIP_TRY(hipEventRecord(c->t1, c->stream));
@@ -979,9 +1216,7 @@ gbs_status gbs_lhaf_device(const gbs_z* A_dev, int32_t N, gbs_precision prec, gb
     st = maybe_tune(c, Np / 2);
     if (st != GBS_OK) return st;
     HIP_TRY(hipStreamWaitEvent(s, c->done, 0));
-    if (Np > 0)
-        HIP_TRY(gbs::launch_prep(reinterpret_cast<const double2*>(A_dev), N, N, Np, c->A0, c->dvec, s));
-    st = run_sum(c, Np, s, reinterpret_cast<double2*>(out_dev), abs_sum_dev, nullptr, prec);
+    st = run_sum(c, reinterpret_cast<const double2*>(A_dev), N, s, reinterpret_cast<double2*>(out_dev), abs_sum_dev, nullptr, prec);
     if (st != GBS_OK) return st;
     HIP_TRY(hipEventRecord(c->done, s));
     return GBS_OK;
@@ -1004,9 +1239,7 @@ gbs_status gbs_lhaf_device_shard(const gbs_z* A_dev, int32_t N, gbs_precision pr
     st = maybe_tune(c, Np / 2);
     if (st != GBS_OK) return st;
     HIP_TRY(hipStreamWaitEvent(s, c->done, 0));
-    if (Np > 0)
-        HIP_TRY(gbs::launch_prep(reinterpret_cast<const double2*>(A_dev), N, N, Np, c->A0, c->dvec, s));
-    st = run_sum(c, Np, s, nullptr, nullptr, nullptr, prec, nullptr, -1, shard, nshards, partial_dev);
+    st = run_sum(c, reinterpret_cast<const double2*>(A_dev), N, s, nullptr, nullptr, nullptr, prec, nullptr, -1, shard, nshards, partial_dev);
     if (st != GBS_OK) return st;
     HIP_TRY(hipEventRecord(c->done, s));
     return GBS_OK;
@@ -1116,7 +1349,10 @@ gbs_status gbs_set_layout(int32_t n, int32_t s, int32_t layout) {
     if (st != GBS_OK) return st;
     for (int nn = (n ? n : 1); nn <= (n ? n : gbs::kMaxPairs); ++nn)
         for (int ss = (s ? s : 1); ss <= (s ? s : nn); ++ss)
-            if (layout < 0 || gbs::charpoly_layout_ok(2 * ss, layout)) c->layout[nn][ss] = c->layout_multi[nn][ss] = layout;
+            if (layout < 0 || gbs::charpoly_layout_ok(2 * ss, layout)) {
+                c->layout[nn][ss] = c->layout_multi[nn][ss] = layout;
+                c->forced[nn][ss] = layout >= 0;
+            }
     return GBS_OK;
 }
 

@@ -11,7 +11,7 @@
 #include <vector>
 
 #include "../../include/gbs_lhaf.h"
-#include "lhaf_kernels.h"
+#include "tree_kernels.h"
 
 namespace gbs_host {
 
@@ -68,6 +68,7 @@ struct DevCtx {
     int layout[gbs::kMaxPairs + 1][gbs::kMaxPairs + 1];
     int layout_multi[gbs::kMaxPairs + 1][gbs::kMaxPairs + 1];
     bool tuned[gbs::kMaxPairs + 1];
+    bool forced[gbs::kMaxPairs + 1][gbs::kMaxPairs + 1] = {};  // lane grid chosen by gbs_set_layout
     char name[64] = {0};
     DevCtx() {
         for (auto& row : layout)
@@ -102,6 +103,48 @@ hipError_t dev_malloc(void** p, size_t bytes);
 // Times each valid lane grid per subset size of an n-pair loop hafnian.
 gbs_status autotune_impl(DevCtx* c, int n, gbs_tune_report* rep);
 
+// ---- subset tree (gbs_host.cpp): FP64 sums without a forced lane grid ----
+
+// How a forest of `items` trees of n pairs is expanded within a memory budget.
+struct TreeSched {
+    int n = 0, levels = 0;       // levels above the nodes that one wavefront finishes
+    uint64_t items = 0, roots = 0;   // trees, and trees expanded at a time
+    uint64_t sub = 0;                // most subtree nodes of one launch
+    uint64_t fold = 1;               // node records folded into one
+    uint64_t records_per_item = 1;   // records per tree
+    uint64_t mid = 0;                // folded records that are folded once more into one (0: they are the result)
+    uint64_t entries = 0;            // series of the entry store
+    uint64_t piece[gbs::kMaxPairs + 1] = {}, off[gbs::kMaxPairs + 2] = {};
+    size_t arena_bytes = 0;
+};
+// Device memory of a schedule: the entry store, with fold > 1 the node records
+// of one launch (S.sub), with mid > 0 that many folded records.
+struct TreeBufs {
+    void* arena = nullptr;
+    double* nodes = nullptr;
+    double* mid = nullptr;
+};
+// False when even one path of the tree does not fit the budget.
+bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records = 1ull << 20);
+// Enqueues the sums of all trees: items * records_per_item records, in item
+// order.  `shard` (nullable) restricts the subsets.  No allocation, no
+// synchronisation.  With `prof`, launches are timed when gbs_profile_enable is
+// on (never under stream capture).
+gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSource& src, const gbs::TreeShard* shard,
+                        double* records, hipStream_t st, int* launches, bool prof);
+// Subsets of shard g of G: colex ranks [C_s g / G, C_s (g + 1) / G) of every size s.
+gbs::TreeShard tree_shard(int n, int shard, int nshards);
+// Share of the subtree nodes that hold one of its subsets.
+double tree_shard_share(const gbs::TreeShard& sh, int n);
+// Whether FP64 sums of n pairs run on the subset tree (gbs_set_layout selects
+// the register-tile kernels instead).
+inline bool tree_route(const DevCtx* c, int n, bool fp32) {
+    if (fp32 || n < 1 || n > gbs::kTreeMaxPairs) return false;
+    for (bool f : c->forced[n])
+        if (f) return false;
+    return true;
+}
+
 // ---- batches of loop hafnians (gbs_batch.cpp) ----
 
 // One persistent per-subset launch of a batch schedule.
@@ -116,6 +159,15 @@ struct CharpolyLaunch {
 struct SeriesLaunch {
     int round, n;
     int block_begin, nblocks;
+};
+
+// Items of a batch that run on the subset tree and have the same n.
+constexpr int kBatchBranches = 4;  // parallel streams of a batch's launches
+struct TreeGroup {
+    TreeSched S;
+    int begin, count;  // range of BatchSchedule::tlist
+    int branch;        // stream, entry store and node records it uses
+    int64_t rec;       // first record
 };
 
 // Host-side schedule of a batch of loop hafnians of dimensions `dims`:
@@ -139,6 +191,12 @@ struct BatchSchedule {
     std::vector<int64_t> pbeg;          // partial records of item i: [pbeg[i], pbeg[i+1])
     std::vector<CharpolyLaunch> cp;
     std::vector<SeriesLaunch> se;
+    std::vector<TreeGroup> tree;        // items on the subset tree, most work first
+    std::vector<int> tlist;             // their indices, grouped
+    size_t tree_arena[kBatchBranches] = {};
+    uint64_t tree_nodes[kBatchBranches] = {};
+    int64_t tree_records = 0;
+    bool tiled = false;                 // some item runs on tiles, as a small item or is empty
     std::vector<int> small;             // FP64 items with 1 <= n <= kSmallPairs, largest n first: one wavefront each
 };
 // tile_offsets: FP64 tiles keep C at the front tile offset of their m (one
@@ -163,10 +221,13 @@ struct BatchDev {
     double2* out = nullptr;
     double* abs = nullptr;
     int* small = nullptr;
+    int* tlist = nullptr;
+    void* tarena[kBatchBranches] = {};
+    double* tnodes[kBatchBranches] = {};
+    double* trec = nullptr;
     const uint64_t* binom = nullptr;  // binomial table (kBinomStride^2)
     const int4* lbmap = nullptr;      // La Budde lane maps (gbs::lb_fill_table)
 };
-constexpr int kBatchBranches = 4;  // parallel streams of the per-subset launches of one round
 // Issues the whole schedule: counter fill, prep, rounds of per-subset launches
 // on the branch streams (joined into `cs` through events from `new_event`),
 // series launches and the per-item reduction, all ordered after prior work on
@@ -174,7 +235,7 @@ constexpr int kBatchBranches = 4;  // parallel streams of the per-subset launche
 // With `prof`, per-subset launches are timed when gbs_profile_enable is on
 // (never under stream capture).
 gbs_status batch_enqueue(DevCtx* c, const BatchSchedule& S, const BatchDev& d, hipStream_t cs, hipStream_t* br,
-                         const std::function<hipError_t(hipEvent_t*)>& new_event, bool prof);
+                         const std::function<hipError_t(hipEvent_t*)>& new_event, bool prof, int* tree_launches = nullptr);
 
 // Per-launch timing (gbs_profile_*): true while profiling is on.
 bool profiling_on();

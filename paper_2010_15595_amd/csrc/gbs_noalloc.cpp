@@ -34,6 +34,10 @@ constexpr size_t kOffRec = kOffPart + 32768;                                   /
 constexpr size_t kRecBytes = size_t(8) << 20;
 constexpr size_t kOffE = kOffRec + kRecBytes;                                  // coefficients of one chunk
 constexpr size_t kEBytes = kScratchBytes - kOffE;
+// subset tree: [entry store | node records of a launch | folded records | records]
+constexpr uint64_t kTreeNodes = 65536, kTreeMid = 4096, kTreeRecords = 8192;
+constexpr size_t kTreeArena = kScratchBytes - kRecord * (kTreeNodes + kTreeMid + kTreeRecords);
+static_assert(kTreeArena % 256 == 0, "aligned records");
 static_assert((kMaxChunk / kBlock) * kRecord <= kOffRec - kOffPart, "chunk partials region");
 static_assert(kScratchBytes == (size_t)GBS_NOALLOC_SCRATCH_BYTES, "header and library agree on the size");
 
@@ -78,6 +82,22 @@ extern "C" gbs_status gbs_lhaf_device_noalloc(const gbs_z* A_dev, int32_t N, gbs
         return GBS_OK;
     }
     char* base = static_cast<char*>(c->na_scratch);
+    if (tree_route(c, n, prec == GBS_FP32_COMP)) {
+        TreeSched S;
+        if (!tree_sched(n, 1, kTreeArena, S, kTreeMid) || (S.fold > 1 && S.sub > kTreeNodes) ||
+            S.records_per_item > kTreeRecords)
+            return fail(GBS_E_TOO_LARGE, "no subset-tree schedule for %d pairs in the scratch array", n);
+        TreeBufs tb;
+        tb.arena = base;
+        tb.nodes = reinterpret_cast<double*>(base + kTreeArena);
+        tb.mid = tb.nodes + 5 * kTreeNodes;
+        double* trec = tb.mid + 5 * kTreeMid;
+        const gbs::TreeSource src{reinterpret_cast<const double2*>(A_dev), nullptr, nullptr, nullptr, N};
+        const gbs_status e = tree_enqueue(S, tb, src, nullptr, trec, st, nullptr, false);
+        if (e != GBS_OK) return e;
+        HIP_TRY(gbs::launch_final_reduce(trec, (int64_t)S.records_per_item, out, abs_sum_dev, st));
+        return GBS_OK;
+    }
     double2* A0 = reinterpret_cast<double2*>(base + kOffA0);
     double2* dv = reinterpret_cast<double2*>(base + kOffD);
     double* part = reinterpret_cast<double*>(base + kOffPart);

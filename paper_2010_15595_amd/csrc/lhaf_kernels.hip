@@ -35,6 +35,7 @@
 // 4x4 (four); the choice per subset size is made by the host (autotuned).
 
 #include "lhaf_device.h"
+#include "tree_launch.h"
 
 namespace gbs {
 // ---------------------------------------------------------------- phase 2
@@ -287,6 +288,7 @@ __global__ void __launch_bounds__(256) batch_prep_kernel(const double2* __restri
                                                          const BatchItem* __restrict__ items) {
     const int i = blockIdx.x;
     const BatchItem it = items[i];
+    if (!it.A0) return;  // runs on the subset tree, from its packed matrix
     const int N = Ns[i], Np = it.Np;
     const double2* A = mats + in_off[i];
     double2* A0 = const_cast<double2*>(it.A0);

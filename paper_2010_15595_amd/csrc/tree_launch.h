@@ -1,0 +1,283 @@
+#pragma once
+// Subset tree: roots, record folds, and the launchers of the kernels of
+// tree_device.h for every n.  Included by lhaf_kernels.hip alone.
+#include "tree_device.h"
+
+namespace gbs {
+
+namespace {
+
+// Level-0 entries of one root: with a = A with zero diagonal, symmetrised, d its
+// diagonal and G the rotation whose rows for pair (i, i + n) are
+// (e_i + e_(i+n)) / sqrt 2 and -i (e_i - e_(i+n)) / sqrt 2, so that G^T G swaps the
+// pair: entry (j, k) = (G a G^T)_jk, entry (j, border) = (G d)_j, constant
+// series.  An odd N gets one more vertex with loop weight 1 and no edges.
+__device__ __forceinline__ double2 at(const double2* A, int N, int r, int c) {
+    if (r == c || r >= N || c >= N) return make_double2(0.0, 0.0);
+    const double2 x = A[r * N + c], y = A[c * N + r];
+    return make_double2(0.5 * (x.x + y.x), 0.5 * (x.y + y.y));
+}
+__device__ __forceinline__ double2 loop_at(const double2* A, int N, int r) {
+    return r < N ? A[r * N + r] : make_double2(1.0, 0.0);
+}
+
+__global__ void __launch_bounds__(64) tree_root_kernel(TreeMap mp, TreeSource src, uint64_t r0, int blocks) {
+    const int n = mp.n, E = tree_entries(n);
+    const unsigned r = blockIdx.x / blocks;
+    const int e = (int)(blockIdx.x % blocks) * 64 + threadIdx.x;
+    if (e >= E) return;
+    const double2* A = src.mats;
+    int N = src.N;
+    if (src.list) {
+        const int i = src.list[r0 + r];
+        A += src.in_off[i];
+        N = src.dims[i];
+    }
+    double2 v = make_double2(0.0, 0.0);
+    if (e > 0) {
+        const int x = e - 1;
+        int j = (int)((__builtin_sqrtf(8.0f * (float)x + 1.0f) - 1.0f) * 0.5f);
+        if (tree_tri(j + 1, 0) <= x) ++j;
+        if (tree_tri(j, 0) > x) --j;
+        const int k = x - tree_tri(j, 0);
+        const int pj = (j - 1) >> 1, pk = (k - 1) >> 1;   // pairs
+        const bool vj = ((j - 1) & 1) != 0, vk = ((k - 1) & 1) != 0;  // second vertex of the pair
+        if (k == 0 && j > 0) {
+            const double2 a = loop_at(A, N, pj), b = loop_at(A, N, pj + n);
+            const double h = 0.70710678118654752440;
+            v = vj ? make_double2(h * (a.y - b.y), -h * (a.x - b.x)) : make_double2(h * (a.x + b.x), h * (a.y + b.y));
+        } else if (k > 0) {
+            const double2 a = at(A, N, pj, pk), b = at(A, N, pj, pk + n);
+            const double2 c = at(A, N, pj + n, pk), d = at(A, N, pj + n, pk + n);
+            const double sb = vk ? -1.0 : 1.0, sc = vj ? -1.0 : 1.0, sd = sb * sc;
+            const double2 s = make_double2(0.5 * ((a.x + sb * b.x) + (sc * c.x + sd * d.x)),
+                                           0.5 * ((a.y + sb * b.y) + (sc * c.y + sd * d.y)));
+            // times 1, -i or (-i)^2
+            v = (vj && vk) ? make_double2(-s.x, -s.y) : ((vj || vk) ? make_double2(s.y, -s.x) : s);
+        }
+    }
+    double2* p = mp.arena + mp.off[0] + (uint64_t)r * (uint64_t)(E * (n + 1)) + e;
+    p[0] = v;
+    for (int k = 1; k <= n; ++k) p[k * E] = make_double2(0.0, 0.0);
+}
+
+// One record (sum re, compensation, sum im, compensation, sum |t|) per `per`
+// records, merged by TwoSum in a fixed tree.
+__global__ void __launch_bounds__(256) records_fold_kernel(const double* __restrict__ in, int64_t np, int64_t per,
+                                                           double* __restrict__ out) {
+    __shared__ double sh[5][256];
+    const int t = threadIdx.x;
+    const int64_t lo = (int64_t)blockIdx.x * per, hi = (lo + per < np) ? lo + per : np;
+    double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    auto merge = [](double* x, const double* y) {
+        const double s = x[0] + y[0], v = s - x[0];
+        x[1] = x[1] + y[1] + ((x[0] - (s - v)) + (y[0] - v));
+        x[0] = s;
+        const double u = x[2] + y[2], w = u - x[2];
+        x[3] = x[3] + y[3] + ((x[2] - (u - w)) + (y[2] - w));
+        x[2] = u;
+        x[4] += y[4];
+    };
+    for (int64_t i = lo + t; i < hi; i += 256) {
+        double b[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) b[q] = in[5 * i + q];
+        merge(a, b);
+    }
+#pragma unroll
+    for (int q = 0; q < 5; ++q) sh[q][t] = a[q];
+    __syncthreads();
+    for (int w = 128; w >= 1; w >>= 1) {
+        if (t < w) {
+            double b[5];
+#pragma unroll
+            for (int q = 0; q < 5; ++q) b[q] = sh[q][t + w];
+            merge(a, b);
+#pragma unroll
+            for (int q = 0; q < 5; ++q) sh[q][t] = a[q];
+        }
+        __syncthreads();
+    }
+    if (t < 5) out[5 * (int64_t)blockIdx.x + t] = sh[t][0];
+}
+
+// Result of item list[i] from its `per` consecutive records (one thread per
+// item for one record, one wavefront otherwise, in a fixed order).
+__global__ void __launch_bounds__(64) tree_items_kernel(const int* __restrict__ list, int count,
+                                                        const double* __restrict__ records, int64_t per,
+                                                        double2* __restrict__ out, double* __restrict__ abs_out) {
+    const int lane = threadIdx.x;
+    if (per <= 1) {
+        const int i = blockIdx.x * 64 + lane;
+        if (i < count) {
+            // no records (per = 0): the empty matrix, loop hafnian 1
+            const double* r = records + 5 * (int64_t)i;
+            out[list[i]] = per ? make_double2(r[0] + r[1], r[2] + r[3]) : make_double2(1.0, 0.0);
+            if (abs_out) abs_out[list[i]] = per ? r[4] : 1.0;
+        }
+        return;
+    }
+    const double* r = records + 5 * per * (int64_t)blockIdx.x;
+    double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    auto merge = [](double* x, const double* y) {
+        const double s = x[0] + y[0], v = s - x[0];
+        x[1] = x[1] + y[1] + ((x[0] - (s - v)) + (y[0] - v));
+        x[0] = s;
+        const double u = x[2] + y[2], w = u - x[2];
+        x[3] = x[3] + y[3] + ((x[2] - (u - w)) + (y[2] - w));
+        x[2] = u;
+        x[4] += y[4];
+    };
+    for (int64_t k = lane; k < per; k += 64) {
+        double b[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) b[q] = r[5 * k + q];
+        merge(a, b);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        double b[5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const int lo = __shfl_xor(__double2loint(a[q]), off), hi = __shfl_xor(__double2hiint(a[q]), off);
+            b[q] = __hiloint2double(hi, lo);
+        }
+        merge(a, b);
+    }
+    if (lane == 0) {
+        out[list[blockIdx.x]] = make_double2(a[0] + a[1], a[2] + a[3]);
+        if (abs_out) abs_out[list[blockIdx.x]] = a[4];
+    }
+}
+
+}  // namespace
+
+constexpr size_t tree_sub_lds(int n) { return 16 * ((size_t)n * kTreeSlots + 128); }
+// LDS series per coefficient of tree_elim_kernel, a compile-time stride chosen by
+// T: the exact one for the three levels that hold most nodes, ranges above.
+constexpr int kElimPlanes[6] = {tree_temps(kTreeDepth), tree_temps(6), tree_temps(7), tree_temps(9), tree_temps(14),
+                                tree_temps(kTreeMaxPairs - 1)};
+
+struct TreeElimArgs {
+    const TreeMap* mp;
+    const TreeShard* sh;
+    int level;
+    uint64_t g0, count;
+    int slices;
+};
+struct TreeSubArgs {
+    const TreeMap* mp;
+    const TreeShard* sh;
+    int level;
+    uint64_t g0, count;
+    double* records;
+};
+
+template <class K>
+inline hipError_t tree_allow_lds(K kernel, size_t bytes) {
+    if (bytes <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)bytes);
+}
+
+template <int NN, int PLANE>
+hipError_t tree_elim_plane(const TreeElimArgs& a, hipStream_t st) {
+    const size_t lds = 16 * (size_t)NN * PLANE;
+    const hipError_t e = tree_allow_lds(tree_elim_kernel<NN, PLANE>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((tree_elim_kernel<NN, PLANE>), dim3((unsigned)(a.count * a.slices)), dim3(64), lds, st, *a.mp,
+                       *a.sh, a.level, a.g0, a.slices);
+    return hipGetLastError();
+}
+template <int NN>
+hipError_t tree_elim_inst(const TreeElimArgs& a, hipStream_t st) {
+    if constexpr (NN > kTreeDepth) {
+        const int T = NN - a.level - 1;
+        if (T == kTreeDepth) return tree_elim_plane<NN, kElimPlanes[0]>(a, st);
+        if constexpr (NN > 6)
+            if (T == 6) return tree_elim_plane<NN, kElimPlanes[1]>(a, st);
+        if constexpr (NN > 7)
+            if (T == 7) return tree_elim_plane<NN, kElimPlanes[2]>(a, st);
+        if constexpr (NN > 8)
+            if (T <= 9) return tree_elim_plane<NN, kElimPlanes[3]>(a, st);
+        if constexpr (NN > 10)
+            if (T <= 14) return tree_elim_plane<NN, kElimPlanes[4]>(a, st);
+        if constexpr (NN > 15) return tree_elim_plane<NN, kElimPlanes[5]>(a, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int NN>
+hipError_t tree_sub_inst(const TreeSubArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(tree_sub_kernel<NN>, dim3((unsigned)a.count), dim3(64), tree_sub_lds(NN), st, *a.mp, *a.sh, a.level, a.g0,
+                       a.records);
+    return hipGetLastError();
+}
+
+// ---- dispatch over n
+
+template <int NN>
+static hipError_t tree_elim_n(int n, const TreeElimArgs& a, hipStream_t st) {
+    if constexpr (NN > kTreeMaxPairs) {
+        return hipErrorInvalidValue;
+    } else {
+        if (n == NN) return tree_elim_inst<NN>(a, st);
+        return tree_elim_n<NN + 1>(n, a, st);
+    }
+}
+template <int NN>
+static hipError_t tree_sub_n(int n, const TreeSubArgs& a, hipStream_t st) {
+    if constexpr (NN > kTreeMaxPairs) {
+        return hipErrorInvalidValue;
+    } else {
+        if (n == NN) return tree_sub_inst<NN>(a, st);
+        return tree_sub_n<NN + 1>(n, a, st);
+    }
+}
+
+int tree_depth(int n) { return n < kTreeDepth ? n : kTreeDepth; }
+
+hipError_t launch_tree_root(const TreeMap& mp, const TreeSource& src, uint64_t r0, uint64_t count, hipStream_t st) {
+    if (count == 0) return hipSuccess;
+    const int blocks = (tree_entries(mp.n) + 63) / 64;
+    hipLaunchKernelGGL(tree_root_kernel, dim3((unsigned)(count * blocks)), dim3(64), 0, st, mp, src, r0, blocks);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_elim(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count,
+                            hipStream_t st) {
+    const int n = mp.n, T = n - level - 1;
+    if (count == 0) return hipSuccess;
+    if (n < 1 || n > kTreeMaxPairs || T < 0) return hipErrorInvalidValue;
+    // couplings of the few nodes near the root over several wavefronts, until
+    // about two per SIMD are in flight
+    const int rounds = (tree_entries(T) - 1 + 63) / 64;
+    const int slices = (int)std::max<uint64_t>(1, std::min<uint64_t>(rounds, 2048 / count));
+    const TreeElimArgs a{&mp, &sh, level, g0, count, slices};
+    return tree_elim_n<1>(n, a, st);
+}
+
+hipError_t launch_tree_sub(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count, double* records,
+                           hipStream_t st) {
+    const int n = mp.n;
+    if (count == 0) return hipSuccess;
+    if (n < 1 || n > kTreeMaxPairs || n - level > kTreeDepth || count > (uint64_t)INT32_MAX) return hipErrorInvalidValue;
+    const TreeSubArgs a{&mp, &sh, level, g0, count, records};
+    return tree_sub_n<1>(n, a, st);
+}
+
+hipError_t launch_records_fold(const double* in, int64_t np, int64_t per, double* out, hipStream_t st) {
+    if (np <= 0) return hipSuccess;
+    hipLaunchKernelGGL(records_fold_kernel, dim3((unsigned)((np + per - 1) / per)), dim3(256), 0, st, in, np, per, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_tree_items(const int* list, int count, const double* records, int64_t per, double2* out,
+                             double* abs_out, hipStream_t st) {
+    if (count <= 0) return hipSuccess;
+    const int grid = per <= 1 ? (count + 63) / 64 : count;
+    hipLaunchKernelGGL(tree_items_kernel, dim3(grid), dim3(64), 0, st, list, count, records, per, out, abs_out);
+    return hipGetLastError();
+}
+
+}  // namespace gbs

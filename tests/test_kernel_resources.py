@@ -112,3 +112,22 @@ def test_benchmark_instances_keep_their_occupancy(kernels, key, waves):
     r = _tiles(kernels)[key]
     assert int(r["Occupancy"]) == waves, (key, r)
     assert int(r["VGPRs"]) + int(r["AGPRs"]) <= 512 // waves
+
+
+def test_subset_tree_kernels_stay_out_of_scratch():
+    """Every subset-tree instance keeps its series in registers."""
+    path = os.path.join(BUILD, "lhaf_kernels.hip.resources.txt")
+    if not os.path.exists(path):
+        pytest.skip("no resource report: run __graft_entry__.build() first")
+    with open(path) as f:
+        text = f.read()
+    names = re.findall(r"Function Name: (\S+)", text)
+    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", text)]
+    assert len(names) == len(scratch)
+    tree = {}
+    for name, x in zip(names, scratch):
+        m = re.search(r"tree_(sub|elim)_kernelILi(\d+)", name)
+        if m:
+            tree.setdefault(m.group(1), set()).add(int(m.group(2)))
+            assert x == 0, name
+    assert tree["sub"] == set(range(1, 29)) and tree["elim"] == set(range(6, 29))
