@@ -319,17 +319,15 @@ std::string charpoly_instance_name(int lay, int s, int D, bool fp32) {
     return buf;
 }
 
-// Subset sum on the LDS-resident kernels (double-double, or FP64 with either
-// characteristic-polynomial method): per size class and chunk, one workgroup
+// FP64 subset sum on the LDS-resident kernels with either characteristic-
+// polynomial method: per size class and chunk, one workgroup
 // per subset writes its term, a block reduction folds them into dd partials,
 // and one final fixed-order dd reduction gives hi (out_dev) and lo (lo_dev).
 gbs_status run_sum_lds(DevCtx* c, int Np, hipStream_t st, double2* out_dev, double2* lo_dev, double* abs_dev,
-                       int* launches, int prec_dd, int method) {
+                       int* launches, int method) {
     const int n = Np / 2, D = n + 1;
-    const int maxp = gbs::lds_max_pairs(prec_dd, method);
-    if (n > maxp)
-        return fail(GBS_E_TOO_LARGE, "%s path: dimension %d exceeds %d",
-                    prec_dd ? "double-double" : "LDS", Np, 2 * maxp);
+    const int maxp = gbs::lds_max_pairs(0, method);
+    if (n > maxp) return fail(GBS_E_TOO_LARGE, "LDS path: dimension %d exceeds %d", Np, 2 * maxp);
     constexpr int kLdsPer = 8;  // terms per lane in the block reduction
     const uint64_t per_block = 64ull * kLdsPer;
     uint64_t max_len = 0, total_blocks = 0;
@@ -341,7 +339,7 @@ gbs_status run_sum_lds(DevCtx* c, int Np, hipStream_t st, double2* out_dev, doub
             total_blocks += (len + per_block - 1) / per_block;
         }
     }
-    gbs_status s1 = ensure_buffer(&c->E, &c->E_cap, (size_t)max_len * gbs::lds_term_bytes(prec_dd), 1);
+    gbs_status s1 = ensure_buffer(&c->E, &c->E_cap, (size_t)max_len * gbs::lds_term_bytes(0), 1);
     if (s1 != GBS_OK) return s1;
     s1 = ensure_buffer((void**)&c->partials, &c->partials_cap, (size_t)total_blocks * 5, sizeof(double));
     if (s1 != GBS_OK) return s1;
@@ -355,13 +353,12 @@ gbs_status run_sum_lds(DevCtx* c, int Np, hipStream_t st, double2* out_dev, doub
             HIP_TRY(timed_launch(
                 kProfCharpoly, subset_flops(n, s) * (double)len, (double)len, st,
                 [&] {
-                    return gbs::launch_charpoly_lds(prec_dd, method, c->A0, c->dvec, Np, s, st0, len, nullptr,
+                    return gbs::launch_charpoly_lds(0, method, c->A0, c->dvec, Np, s, st0, len, nullptr,
                                                     c->binom, D, sign, c->E, st);
                 },
-                prec_dd ? "charpoly_lds_kernel<ArDD, 0>"
-                        : (method == gbs::kCharpolyEigen ? "charpoly_lds_kernel<ArF64, 1>" : "charpoly_lds_kernel<ArF64, 0>")));
+                method == gbs::kCharpolyEigen ? "charpoly_lds_kernel<ArF64, 1>" : "charpoly_lds_kernel<ArF64, 0>"));
             HIP_TRY(timed_launch(kProfSeries, 0.0, (double)len, st, [&] {
-                return gbs::launch_lds_block_reduce(prec_dd, c->E, len, kLdsPer, c->partials + 5 * poff, nullptr, st);
+                return gbs::launch_lds_block_reduce(0, c->E, len, kLdsPer, c->partials + 5 * poff, nullptr, st);
             }));
             poff += (len + per_block - 1) / per_block;
             nl += 2;
@@ -408,12 +405,12 @@ uint64_t piece_entries(TreeSched& S, int full, uint64_t sub) {
 
 }  // namespace
 
-bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records) {
+bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records, int depth, size_t value) {
     S = TreeSched();
     S.n = n;
     S.items = items;
-    S.levels = n - gbs::tree_depth(n);
-    const size_t entry = 16 * (size_t)(n + 1);
+    S.levels = n - depth;
+    const size_t entry = value * (size_t)(n + 1);
     const uint64_t most = budget / entry;
     // roots in flight: all their levels when they fit
     uint64_t per = gbs::tree_entries(n);
@@ -609,6 +606,65 @@ gbs_status run_sum_tree(DevCtx* c, const double2* A, int N, hipStream_t st, doub
     return GBS_OK;
 }
 
+// Double-double subset sum on the subset tree, level by level down to the
+// leaves, whose terms are folded like those of the LDS-resident kernels.
+gbs_status run_sum_tree_dd(DevCtx* c, const double2* A, int N, hipStream_t st, double2* out_dev, double2* lo_dev,
+                           double* abs_dev, int* launches) {
+    const int n = (N + 1) / 2;
+    if (n > gbs::kMaxDdPairs)
+        return fail(GBS_E_TOO_LARGE, "double-double path: dimension %d exceeds %d", 2 * n, 2 * gbs::kMaxDdPairs);
+    constexpr int kPer = 8;  // terms per lane in the block reduction
+    const uint64_t per_block = 64ull * kPer;
+    const size_t value = gbs::lds_term_bytes(1);
+    TreeSched S;
+    if (!tree_sched(n, 1, kTreeBudget, S, UINT64_MAX, 0, value))
+        return fail(GBS_E_TOO_LARGE, "no double-double schedule for %d pairs", n);
+    gbs_status s1 = ensure_buffer(&c->E, &c->E_cap, S.arena_bytes + S.sub * value, 1);
+    if (s1 != GBS_OK) return s1;
+    const uint64_t blocks = (1ull << n) / S.sub * ((S.sub + per_block - 1) / per_block);
+    s1 = ensure_buffer((void**)&c->partials, &c->partials_cap, blocks * 5, sizeof(double));
+    if (s1 != GBS_OK) return s1;
+    void* terms = static_cast<char*>(c->E) + S.arena_bytes;
+    gbs::TreeMap mp{};
+    mp.arena = static_cast<double2*>(c->E);
+    mp.n = n;
+    for (int lv = 0; lv <= n; ++lv) mp.off[lv] = S.off[lv] * (uint64_t)(n + 1);
+    HIP_TRY(gbs::launch_tree_dd_root(mp, A, N, st));
+    int nl = 1;
+    uint64_t poff = 0;
+    std::function<gbs_status(int, uint64_t, uint64_t)> run = [&](int lv, uint64_t g0, uint64_t count) -> gbs_status {
+        if (lv == n) {
+            HIP_TRY(timed_launch(
+                kProfCharpoly, gbs_yardstick_flops(2 * n) * (double)count / (double)(1ull << n), (double)count, st,
+                [&] { return gbs::launch_tree_dd_leaf(mp, g0, count, terms, st); }, "tree_dd_leaf_kernel"));
+            HIP_TRY(timed_launch(kProfSeries, 0.0, (double)count, st, [&] {
+                return gbs::launch_lds_block_reduce(1, terms, count, kPer, c->partials + 5 * poff, nullptr, st);
+            }));
+            poff += (count + per_block - 1) / per_block;
+            nl += 2;
+            return GBS_OK;
+        }
+        for (uint64_t q = 0; q < count; q += S.piece[lv]) {
+            const uint64_t len = std::min(S.piece[lv], count - q);
+            mp.win[lv + 1] = g0 + q;
+            HIP_TRY(timed_launch(
+                kProfCharpoly, 0.0, 0.0, st, [&] { return gbs::launch_tree_dd_elim(mp, lv, g0 + q, len, st); },
+                "tree_dd_elim_kernel"));
+            ++nl;
+            const gbs_status e = run(lv + 1, 2 * (g0 + q), 2 * len);
+            if (e != GBS_OK) return e;
+        }
+        return GBS_OK;
+    };
+    const gbs_status e = run(0, 0, 1);
+    if (e != GBS_OK) return e;
+    HIP_TRY(timed_launch(kProfReduce, 0.0, 0.0, st, [&] {
+        return gbs::launch_dd_final_reduce(c->partials, (int64_t)poff, out_dev, lo_dev, abs_dev, st);
+    }));
+    if (launches) *launches = nl + 1;
+    return GBS_OK;
+}
+
 // A shard's ranks of the size classes are scattered over the subset tree, so the
 // nodes that hold any of its subsets are share * G times its share of the
 // subsets (1.3 for two shards, 1.9 to 3.3 for the outer and middle ones of
@@ -616,7 +672,8 @@ gbs_status run_sum_tree(DevCtx* c, const double2* A, int N, hipStream_t st, doub
 // register-tile kernels do just its subsets, each at several times the cost.
 constexpr double kTreeShardCost = 3.4;
 
-// lds_method >= 0 selects the LDS-resident kernels with that characteristic-polynomial method.
+// lds_method >= 0 selects the LDS-resident FP64 kernels with that characteristic-polynomial
+// method; double-double sums all run on the subset tree.
 // Shard g of G (FP64 / FP32 paths only) sums its ranks of every class; with
 // record_dev set, the compensated partial (sum, compensation re / im, sum |t|)
 // is written there instead of the rounded result.
@@ -642,10 +699,9 @@ gbs_status run_sum(DevCtx* c, const double2* A, int N, hipStream_t st, double2* 
     bool tree = prec == GBS_FP64 && lds_method < 0 && tree_route(c, n, false);
     if (tree && nshards > 1)
         tree = tree_shard_share(tree_shard(n, shard, nshards), n) * nshards <= kTreeShardCost;
+    if (prec == GBS_DD) return run_sum_tree_dd(c, A, N, st, out_dev, lo_dev, abs_dev, launches);
     if (!tree) HIP_TRY(gbs::launch_prep(A, N, N, Np, c->A0, c->dvec, st));
-    if (prec == GBS_DD || lds_method >= 0)
-        return run_sum_lds(c, Np, st, out_dev, lo_dev, abs_dev, launches, prec == GBS_DD ? 1 : 0,
-                           lds_method >= 0 ? lds_method : gbs::kCharpolyLaBudde);
+    if (lds_method >= 0) return run_sum_lds(c, Np, st, out_dev, lo_dev, abs_dev, launches, lds_method);
     if (lo_dev) HIP_TRY(gbs::launch_scalar_set(lo_dev, make_double2(0.0, 0.0), nullptr, 0.0, st));
     const bool fp32 = prec == GBS_FP32_COMP;
     if (tree) return run_sum_tree(c, A, N, st, out_dev, abs_dev, launches, shard, nshards, record_dev);

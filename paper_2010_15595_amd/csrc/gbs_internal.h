@@ -124,8 +124,12 @@ struct TreeBufs {
     double* nodes = nullptr;
     double* mid = nullptr;
 };
-// False when even one path of the tree does not fit the budget.
-bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records = 1ull << 20);
+// False when even one path of the tree does not fit the budget.  Levels down to
+// the nodes with `depth` pairs left, `value` bytes per coefficient.
+bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records, int depth, size_t value);
+inline bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records = 1ull << 20) {
+    return tree_sched(n, items, budget, S, mid_records, gbs::tree_depth(n), sizeof(double2));
+}
 // Enqueues the sums of all trees: items * records_per_item records, in item
 // order.  `shard` (nullable) restricts the subsets.  No allocation, no
 // synchronisation.  With `prof`, launches are timed when gbs_profile_enable is

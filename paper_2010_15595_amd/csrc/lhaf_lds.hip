@@ -16,6 +16,7 @@
 
 #include "dd.h"
 #include "lhaf_kernels.h"
+#include "tree_dd.h"
 
 namespace gbs {
 

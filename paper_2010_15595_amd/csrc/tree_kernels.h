@@ -53,4 +53,11 @@ hipError_t launch_records_fold(const double* in, int64_t np, int64_t per, double
 hipError_t launch_tree_items(const int* list, int count, const double* records, int64_t per, double2* out,
                              double* abs_out, hipStream_t st);
 
+// ---- double-double (tree_dd.h): blocks of cdd values, one matrix, down to the
+// leaves (level n)
+hipError_t launch_tree_dd_root(const TreeMap& mp, const double2* A, int N, hipStream_t st);
+hipError_t launch_tree_dd_elim(const TreeMap& mp, int level, uint64_t g0, uint64_t count, hipStream_t st);
+// Signed terms (double-double) of subset masks g0 .. g0 + count - 1.
+hipError_t launch_tree_dd_leaf(const TreeMap& mp, uint64_t g0, uint64_t count, void* terms, hipStream_t st);
+
 }  // namespace gbs

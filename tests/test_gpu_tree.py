@@ -89,3 +89,20 @@ def test_nan_entries_reach_the_result():
         gbs.lhaf_device(torch.from_numpy(A).cuda(), o)
         torch.cuda.synchronize()
         assert np.isnan(complex(o.cpu()[0]).real)
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 9, 30, 32, 33, 35, 43, 49])
+def test_double_double(N):
+    """Orders on both sides of the switch from 16 to 32 lanes per solve (n = 16 /
+    17), of the row kept in LDS or in memory and of one or several parents per
+    workgroup: a permuted matrix (other subsets, other rounding) gives the same
+    value to double-double accuracy, and the FP64 sum agrees to its own."""
+    A = _matrix(N)
+    p = np.random.default_rng(N).permutation(N)
+    v, d = gbs.lhaf(A, prec=gbs.GBS_DD, with_diag=True)
+    w, e = gbs.lhaf(np.ascontiguousarray(A[np.ix_(p, p)]), prec=gbs.GBS_DD, with_diag=True)
+    f, g = gbs.lhaf(A, with_diag=True)
+    # the two splits have different sum_S |t_S|; each value is good to 2e-30 of its own
+    assert abs((v - w) + (d["lhaf_lo"] - e["lhaf_lo"])) <= 2e-30 * (d["abs_sum"] + e["abs_sum"])
+    assert abs(f - v) <= NORMWISE * d["abs_sum"]
+    assert d["abs_sum"] == pytest.approx(g["abs_sum"], rel=1e-12)

@@ -131,3 +131,15 @@ def test_subset_tree_kernels_stay_out_of_scratch():
             tree.setdefault(m.group(1), set()).add(int(m.group(2)))
             assert x == 0, name
     assert tree["sub"] == set(range(1, 29)) and tree["elim"] == set(range(6, 29))
+
+
+def test_double_double_tree_kernels_stay_out_of_scratch():
+    path = os.path.join(BUILD, "lhaf_lds.hip.resources.txt")
+    if not os.path.exists(path):
+        pytest.skip("no resource report: run __graft_entry__.build() first")
+    with open(path) as f:
+        text = f.read()
+    names = re.findall(r"Function Name: (\S+)", text)
+    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", text)]
+    found = [x for name, x in zip(names, scratch) if "tree_dd_" in name]
+    assert len(found) == 4 and not any(found)
