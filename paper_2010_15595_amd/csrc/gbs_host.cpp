@@ -387,17 +387,15 @@ RankRange shard_ranks(uint64_t cnt, int g, int G) {
 namespace {
 
 // Parents of each level expanded by one launch, and the entries that takes.
-// Below `full` every level is expanded whole; from there on in pieces that
-// feed `sub` nodes to one launch of the subtree kernel.
-uint64_t piece_entries(TreeSched& S, int full, uint64_t sub) {
+// Whole levels when `sub` is all nodes, else pieces that feed `sub` nodes to one
+// launch of the subtree kernel.
+uint64_t piece_entries(TreeSched& S, uint64_t sub) {
     const int L = S.levels;
     uint64_t e = S.roots * (uint64_t)gbs::tree_entries(S.n);
-    S.off[0] = 0;
     for (int lv = 0; lv < L; ++lv) {
         const uint64_t whole = S.roots << lv;
         const int sh = L - lv;
-        S.piece[lv] = lv < full ? whole : std::min<uint64_t>(whole, std::max<uint64_t>(1, sh < 63 ? sub >> sh : 0));
-        S.off[lv + 1] = e;
+        S.piece[lv] = std::min<uint64_t>(whole, std::max<uint64_t>(1, sh < 63 ? sub >> sh : 0));
         e += S.piece[lv] * (uint64_t)gbs::tree_entries(S.n - lv - 1);
     }
     return e;
@@ -417,17 +415,36 @@ bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid
     for (int lv = 0; lv < S.levels; ++lv) per += (uint64_t)gbs::tree_entries(n - lv - 1) << lv;
     S.roots = std::max<uint64_t>(1, std::min<uint64_t>(items, most / per));
     uint64_t sub = S.roots << S.levels;
-    if (piece_entries(S, S.levels, sub) > most) {
-        uint64_t p2 = 1;
-        while (p2 * 2 <= sub) p2 *= 2;
-        sub = p2;
-        while (sub > 1 && piece_entries(S, 0, sub) > most - most / 4) sub /= 2;
-        if (piece_entries(S, 0, sub) > most) return false;
-        int full = 0;
-        while (full < S.levels && piece_entries(S, full + 1, sub) <= most) ++full;
-        S.entries = piece_entries(S, full, sub);
-    } else {
-        S.entries = piece_entries(S, S.levels, sub);
+    S.entries = piece_entries(S, sub);
+    if (S.entries > most) {  // one root: powers of two throughout
+        // a quarter is left for longer pieces above, unless the subtree kernel then
+        // gets fewer wavefronts than the chip holds
+        do {
+            if (sub == 1) return false;
+            sub /= 2;
+            S.entries = piece_entries(S, sub);
+        } while (S.entries > (sub > 1024 ? most - most / 4 : most));
+        // longer pieces where they save the most launches per entry
+        for (;;) {
+            int best = -1;
+            double gain = 0.0;
+            uint64_t extra = 0;
+            for (int lv = 0; lv < S.levels - 1; ++lv) {
+                const uint64_t p = S.piece[lv], add = p * (uint64_t)gbs::tree_entries(n - lv - 1);
+                if (p >= (1ull << lv) || (lv > 0 && p >= 2 * S.piece[lv - 1]) || S.entries + add > most) continue;
+                const double g = (double)((1ull << lv) / p) / (double)add;
+                if (best < 0 || g > gain) best = lv, gain = g, extra = add;
+            }
+            if (best < 0) break;
+            S.piece[best] *= 2;
+            S.entries += extra;
+        }
+    }
+    S.off[0] = 0;
+    uint64_t end = S.roots * (uint64_t)gbs::tree_entries(n);
+    for (int lv = 0; lv < S.levels; ++lv) {
+        S.off[lv + 1] = end;
+        end += S.piece[lv] * (uint64_t)gbs::tree_entries(n - lv - 1);
     }
     S.sub = S.levels ? 2 * S.piece[S.levels - 1] : S.roots;
     S.arena_bytes = S.entries * entry;

@@ -35,7 +35,7 @@ constexpr size_t kRecBytes = size_t(8) << 20;
 constexpr size_t kOffE = kOffRec + kRecBytes;                                  // coefficients of one chunk
 constexpr size_t kEBytes = kScratchBytes - kOffE;
 // subset tree: [entry store | node records of a launch | folded records | records]
-constexpr uint64_t kTreeNodes = 65536, kTreeMid = 4096, kTreeRecords = 8192;
+constexpr uint64_t kTreeNodes = 2048, kTreeMid = 2048, kTreeRecords = 2048;
 constexpr size_t kTreeArena = kScratchBytes - kRecord * (kTreeNodes + kTreeMid + kTreeRecords);
 static_assert(kTreeArena % 256 == 0, "aligned records");
 static_assert((kMaxChunk / kBlock) * kRecord <= kOffRec - kOffPart, "chunk partials region");

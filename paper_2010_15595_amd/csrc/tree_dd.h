@@ -11,7 +11,7 @@
 // N = 28 5.67 -> 0.55 ms, N = 36 94 -> 6.7 ms, N = 41 1030 -> 60 ms.
 // Included by lhaf_lds.hip alone (floating-point contraction is off there).
 #include "dd.h"
-#include "tree_device.h"
+#include "tree_lane.h"
 
 namespace gbs {
 
@@ -41,148 +41,25 @@ __device__ __forceinline__ void mac(Acc& c, const cdd& a, const cdd& b) {
     term(c.ih, c.il, a.im.hi, a.im.lo, b.re.hi, b.re.lo);
 }
 
-// Block of a node (coefficient k of entry e at base[k stride + e]).
-struct Block {
-    cdd* base;
-    int stride;
+constexpr int kThreads = treelane::kThreads;
+
+struct Arith {
+    using V = cdd;
+    using Acc = treedd::Acc;
+    static constexpr int kUnroll = 1;
+    static __device__ __forceinline__ Acc acc_of(const V& a) { return treedd::acc_of(a); }
+    static __device__ __forceinline__ V value(const Acc& a) { return treedd::value(a); }
+    static __device__ __forceinline__ void mac(Acc& c, const V& a, const V& b) { treedd::mac(c, a, b); }
+    static __device__ __forceinline__ V scale(const V& a, double x) { return cdd_mul_d(a, x); }
+    static __device__ __forceinline__ V add(const V& a, const V& b) { return cdd_add(a, b); }
+    template <int I>
+    static __device__ __forceinline__ V bcast(const V& a) {
+        return cdd{dd{treelane::row_bcast<I>(a.re.hi), treelane::row_bcast<I>(a.re.lo)},
+                   dd{treelane::row_bcast<I>(a.im.hi), treelane::row_bcast<I>(a.im.lo)}};
+    }
 };
-__device__ __forceinline__ Block node_block(const TreeMap& mp, int level, uint64_t g) {
-    const uint64_t b = g & ((1ull << level) - 1ull);
-    const int z = b ? __builtin_ctzll(b) : level;
-    const int lv = level - z;
-    const uint64_t slot = b ? (g >> z) >> 1 : g >> level;
-    const int E = tree_entries(mp.n - lv);
-    return Block{reinterpret_cast<cdd*>(mp.arena) + mp.off[lv] + (slot - mp.win[lv]) * (uint64_t)(E * (mp.n + 1)), E};
-}
-
-constexpr int kThreads = 256;      // 16 or 8 solves at a time
-constexpr int kWideThreads = 512;   // a node on several workgroups: what each repeats should be short
-
-// A solve runs on 16 or 32 lanes, one per coefficient (n <= 31).
-__host__ __device__ constexpr int solve_lanes(int n) { return n <= 16 ? 16 : 32; }
-__host__ __device__ constexpr int lds_stride(int n) { return n | 1; }  // odd: spreads the series over the banks
-// LDS series per node: y (W + 1, the last y_v), z (W), the power sums of the two
-// vertices, the updated row of v (W + 2), and with `rows` the row of u (W + 1)
-__host__ __device__ constexpr int lds_series(int T, bool rows) {
-    return 3 * (2 * T + 1) + 5 + (rows ? 2 * T + 2 : 0);
-}
 
 }  // namespace treedd
-
-// Include children of parents g0 .. g0 + count - 1 of `level`, `per` parents per
-// workgroup; gridDim.y workgroups share the couplings of the same parents and
-// each repeat the solves.  ROWS: the row of u is copied to LDS; otherwise it is
-// read from the parent's block (the row of v, which changes, always moves to LDS).
-template <bool ROWS>
-__global__ void __launch_bounds__(treedd::kWideThreads) tree_dd_elim_kernel(TreeMap mp, int level, uint64_t g0,
-                                                                            uint64_t count, int per) {
-    using namespace treedd;
-    extern __shared__ double4 lds_dd[];
-    cdd* lds = reinterpret_cast<cdd*>(lds_dd);
-    const int n = mp.n, T = n - level - 1, W = 2 * T + 1, E = tree_entries(T), R = 2 * W + 3;
-    const int ns = lds_stride(n), sl = lds_series(T, ROWS), P = solve_lanes(n);
-    const int tid = threadIdx.x, NT = blockDim.x, kl = tid & (P - 1);
-    const uint64_t first = (uint64_t)blockIdx.x * per;
-    const int nodes = (int)min((uint64_t)per, count - first);
-    auto parent = [&](int c) { return treedd::node_block(mp, level, g0 + first + c); };
-    auto child = [&](int c) {
-        return Block{reinterpret_cast<cdd*>(mp.arena) + mp.off[level + 1] +
-                         (g0 + first + c - mp.win[level + 1]) * (uint64_t)(E * (n + 1)),
-                     E};
-    };
-    auto y_at = [&](int c, int j, int k) -> cdd& { return lds[((c * sl) + j) * ns + k]; };              // j <= W
-    auto z_at = [&](int c, int j, int k) -> cdd& { return lds[((c * sl) + W + 1 + j) * ns + k]; };      // j < W
-    auto p_at = [&](int c, int q, int k) -> cdd& { return lds[((c * sl) + 2 * W + 1 + q) * ns + k]; };  // q < 2
-    // row of u: u_j (j <= W, the last m_uu); row of v: v_j (j <= W + 1: m_uv, m_vv)
-    auto v_at = [&](int c, int j, int k) -> cdd& { return lds[((c * sl) + 2 * W + 3 + j) * ns + k]; };
-    auto u_at = [&](int c, const Block& pb, int j, int k) -> const cdd& {
-        return ROWS ? lds[((c * sl) + 3 * W + 5 + j) * ns + k] : pb.base[k * pb.stride + E + j];
-    };
-    {
-        const int r0 = ROWS ? 0 : W + 1, Q = R - r0;
-        for (int q = tid; q < nodes * Q * n; q += NT) {
-            const int c = q / (Q * n), x = q - c * (Q * n), k = x / Q, r = r0 + x - k * Q;
-            const Block pb = parent(c);
-            lds[((c * sl) + (r <= W ? 3 * W + 5 + r : W + 2 + r)) * ns + k] = pb.base[k * pb.stride + E + r];
-        }
-        __syncthreads();
-    }
-    for (int ph = 0; ph < 2; ++ph) {
-        // y_j = m_uj / (1 - x m_uu), j < W and j = W (v), then z_j with the updated row
-        // of v; j = -1: the power sums.  Lane k accumulates coefficient k; coefficient i
-        // is complete at step i and handed to the others through LDS.
-        const int solves = ph == 0 ? W + 2 : W + 1;
-        for (int t0 = 0; t0 < nodes * solves; t0 += NT / P) {
-            const int t = t0 + tid / P;
-            const bool on = t < nodes * solves;
-            const int c = on ? t / solves : 0, j = on ? t - c * solves - 1 : 0;
-            const Block pb = parent(c);
-            auto pivot = [&](int k) -> const cdd& { return ph == 0 ? u_at(c, pb, W, k) : v_at(c, W + 1, k); };
-            cdd* out = j < 0 ? &p_at(c, ph, 0) : (ph == 0 ? &y_at(c, j, 0) : &z_at(c, j, 0));
-            const bool mine = on && kl < n;
-            Acc a{0.0, 0.0, 0.0, 0.0};
-            if (mine) {
-                if (j < 0) a = acc_of(cdd_mul_d(pivot(kl), (double)(kl + 1)));
-                else if (ph == 0 && j < W) a = acc_of(u_at(c, pb, j, kl));
-                else a = acc_of(v_at(c, j, kl));
-            }
-            for (int i = 0; i < n; ++i) {
-                if (mine && kl == i) out[i] = value(a);
-                tree::order_wave();
-                if (mine && kl > i) treedd::mac(a, out[i], pivot(kl - 1 - i));
-            }
-        }
-        __syncthreads();
-        if (ph == 0) {
-            // row of v: m_vj + x y_v m_uj (j < W), m_vv + x y_v m_uv; lanes of one
-            // coefficient together.  m_uv itself stays.
-            const int rows = nodes * (W + 1);
-            for (int t = tid; t < rows * n; t += NT) {
-                const int k = t / rows, q = t - k * rows, c = q / (W + 1), x = q - c * (W + 1);
-                const Block pb = parent(c);
-                const int j = x < W ? x : W + 1;
-                Acc a = acc_of(v_at(c, j, k));
-                for (int i = 0; i < k; ++i)
-                    treedd::mac(a, y_at(c, W, i), x < W ? u_at(c, pb, x, k - 1 - i) : v_at(c, W, k - 1 - i));
-                v_at(c, j, k) = value(a);
-            }
-            __syncthreads();
-        }
-    }
-    if (blockIdx.y == 0)
-        for (int t = tid; t < nodes * n; t += NT) {
-        const int c = t / n, k = t - c * n;
-        const Block pb = parent(c), cb = child(c);
-        cb.base[k * cb.stride] = cdd_add(pb.base[k * pb.stride], cdd_add(p_at(c, 0, k), p_at(c, 1, k)));
-    }
-    // the children's couplings m_jk + x y_j m_uk + x z_j m_vk (the border's own held
-    // times x, n + 1 coefficients)
-    const int D = E - 1, all = nodes * D;
-    for (int t = blockIdx.y * NT + tid; t < all * n + nodes; t += NT * gridDim.y) {
-        int k, c, x;
-        if (t < all * n) {
-            k = t / all;
-            const int q = t - k * all;
-            c = q / D;
-            x = q - c * D;
-        } else {
-            k = n;
-            c = t - all * n;
-            x = 0;
-        }
-        const Block pb = parent(c), cb = child(c);
-        int j = (int)((__builtin_sqrtf(8.0f * (float)x + 1.0f) - 1.0f) * 0.5f);
-        if (tree_tri(j + 1, 0) <= x) ++j;
-        if (tree_tri(j, 0) > x) --j;
-        const int k0 = x - tree_tri(j, 0);
-        Acc a = acc_of(pb.base[k * pb.stride + 1 + x]);
-        for (int i = 0; i < k; ++i) {
-            treedd::mac(a, y_at(c, j, i), u_at(c, pb, k0, k - 1 - i));
-            treedd::mac(a, z_at(c, j, i), v_at(c, k0, k - 1 - i));
-        }
-        cb.base[k * cb.stride + 1 + x] = value(a);
-    }
-}
 
 // Signed terms of the leaves g0 .. g0 + count - 1 (subset masks), one on as many
 // lanes as a solve: k e_k = sum_j (p_j + j q_j) / 2 e_(k-j), lane k - 1 holding e_k.
@@ -190,11 +67,11 @@ __global__ void __launch_bounds__(treedd::kThreads) tree_dd_leaf_kernel(TreeMap 
                                                                         cdd* __restrict__ terms) {
     using namespace treedd;
     __shared__ cdd f[2 * kThreads], e[2 * kThreads];  // kThreads / P groups of P + 1
-    const int n = mp.n, P = solve_lanes(n), grp = threadIdx.x / P, k = (threadIdx.x & (P - 1)) + 1;
+    const int n = mp.n, P = treelane::solve_lanes(n), grp = threadIdx.x / P, k = (threadIdx.x & (P - 1)) + 1;
     const uint64_t i0 = (uint64_t)blockIdx.x * (kThreads / P) + grp;
     if (i0 >= count) return;
     const uint64_t g = g0 + i0;
-    const Block b = treedd::node_block(mp, n, g);
+    const treelane::Block<cdd> b = treelane::node_block<cdd>(mp, n, g);
     cdd *fs = f + grp * (P + 1), *es = e + grp * (P + 1);
     const bool mine = k <= n;
     if (mine) {
@@ -264,42 +141,19 @@ hipError_t launch_tree_dd_root(const TreeMap& mp, const double2* A, int N, hipSt
     return hipGetLastError();
 }
 
+// Up to here a parent's row of lanes per series is faster than several parents
+// packed into a workgroup: N = 28 with a limit of 32, 128, 256, 512, 1024:
+// 531, 520, 521, 540, 565 us.
+constexpr uint64_t kTopParentsDd = 256;
+
 hipError_t launch_tree_dd_elim(const TreeMap& mp, int level, uint64_t g0, uint64_t count, hipStream_t st) {
-    const int n = mp.n, T = n - level - 1;
-    if (count == 0) return hipSuccess;
-    if (n < 1 || n > kMaxDdPairs || T < 0) return hipErrorInvalidValue;
-    static_assert(kMaxDdPairs <= 31, "a coefficient per lane of a half wavefront");
-    const size_t series = sizeof(cdd) * (size_t)treedd::lds_stride(n);
-    // Several wide workgroups per parent while there are fewer parents than two per
-    // CU (N = 28: 0.55 ms with them, 0.90 ms with one workgroup each); the row of u in
-    // LDS while a node's series take at most 64 KB; then as many nodes per
-    // workgroup as fit 32 KB (five workgroups per CU).  N = 41: 60.9 ms; with 16, 24
-    // or 40 KB 65.7, 62.6, 64.2 ms; with 128 threads 73.3, with 512 67.4 ms; with the
-    // row of u always in memory 66.2 ms.
-    const uint64_t units = (uint64_t)(tree_entries(T) - 1) * n;
-    const unsigned slices =
-        (unsigned)std::max<uint64_t>(1, std::min<uint64_t>((units + treedd::kWideThreads - 1) / treedd::kWideThreads, 512 / count));
-    const bool rows = series * treedd::lds_series(T, true) <= 64 * 1024;
-    const size_t node = series * treedd::lds_series(T, rows);
-    const bool wide = count <= 512 && units > treedd::kThreads;
-    const int per = wide ? 1 : (int)std::min<uint64_t>(count, std::max<size_t>(1, std::min<size_t>(16, 32 * 1024 / node)));
-    const size_t lds = node * per;
-    static_assert(sizeof(cdd) * treedd::lds_stride(kMaxDdPairs) * treedd::lds_series(kMaxDdPairs - 1, false) <= 160 * 1024,
-                  "LDS of the largest elimination");
-    const auto k = rows ? tree_dd_elim_kernel<true> : tree_dd_elim_kernel<false>;
-    if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k, dim3((unsigned)((count + per - 1) / per), wide ? slices : 1),
-                       dim3(wide ? treedd::kWideThreads : treedd::kThreads), lds, st, mp, level, g0, count, per);
-    return hipGetLastError();
+    if (count <= kTopParentsDd) return launch_tree_top_elim<treedd::Arith>(mp, level, g0, count, st);
+    return launch_tree_lane_elim<treedd::Arith>(mp, level, g0, count, st);
 }
 
 hipError_t launch_tree_dd_leaf(const TreeMap& mp, uint64_t g0, uint64_t count, void* terms, hipStream_t st) {
     if (count == 0) return hipSuccess;
-    const unsigned per = (unsigned)(treedd::kThreads / treedd::solve_lanes(mp.n));
+    const unsigned per = (unsigned)(treedd::kThreads / treelane::solve_lanes(mp.n));
     hipLaunchKernelGGL(tree_dd_leaf_kernel, dim3((unsigned)((count + per - 1) / per)), dim3(treedd::kThreads), 0, st, mp,
                        g0, count, static_cast<cdd*>(terms));
     return hipGetLastError();

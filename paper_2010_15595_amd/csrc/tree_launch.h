@@ -1,7 +1,7 @@
 #pragma once
 // Subset tree: roots, record folds, and the launchers of the kernels of
 // tree_device.h for every n.  Included by lhaf_kernels.hip alone.
-#include "tree_device.h"
+#include "tree_lane.h"
 
 namespace gbs {
 
@@ -154,9 +154,11 @@ __global__ void __launch_bounds__(64) tree_items_kernel(const int* __restrict__ 
 
 constexpr size_t tree_sub_lds(int n) { return 16 * ((size_t)n * kTreeSlots + 128); }
 // LDS series per coefficient of tree_elim_kernel, a compile-time stride chosen by
-// T: the exact one for the three levels that hold most nodes, ranges above.
+// T: the exact one for the three levels that hold most nodes, ranges above, up to
+// the last level of a launch with more than kTopParents parents at n = 28.
+constexpr int kElimPairs = 19;
 constexpr int kElimPlanes[6] = {tree_temps(kTreeDepth), tree_temps(6), tree_temps(7), tree_temps(9), tree_temps(14),
-                                tree_temps(kTreeMaxPairs - 1)};
+                                tree_temps(kElimPairs)};
 
 struct TreeElimArgs {
     const TreeMap* mp;
@@ -202,7 +204,8 @@ hipError_t tree_elim_inst(const TreeElimArgs& a, hipStream_t st) {
             if (T <= 9) return tree_elim_plane<NN, kElimPlanes[3]>(a, st);
         if constexpr (NN > 10)
             if (T <= 14) return tree_elim_plane<NN, kElimPlanes[4]>(a, st);
-        if constexpr (NN > 15) return tree_elim_plane<NN, kElimPlanes[5]>(a, st);
+        if constexpr (NN > 15)
+            if (T <= kElimPairs) return tree_elim_plane<NN, kElimPlanes[5]>(a, st);
     }
     return hipErrorInvalidValue;
 }
@@ -244,13 +247,40 @@ hipError_t launch_tree_root(const TreeMap& mp, const TreeSource& src, uint64_t r
     return hipGetLastError();
 }
 
+namespace treelane {
+struct F64 {
+    using V = double2;
+    using Acc = double2;
+    static constexpr int kUnroll = 4;
+    static __device__ __forceinline__ Acc acc_of(const V& a) { return a; }
+    static __device__ __forceinline__ V value(const Acc& a) { return a; }
+    static __device__ __forceinline__ void mac(Acc& c, const V& a, const V& b) { c = tree::mac(a, b, c); }
+    static __device__ __forceinline__ V scale(const V& a, double x) { return make_double2(a.x * x, a.y * x); }
+    static __device__ __forceinline__ V add(const V& a, const V& b) { return make_double2(a.x + b.x, a.y + b.y); }
+    template <int I>
+    static __device__ __forceinline__ V bcast(const V& a) {
+        return make_double2(treelane::row_bcast<I>(a.x), treelane::row_bcast<I>(a.y));
+    }
+};
+}  // namespace treelane
+
+// Up to here a launch of tree_elim_kernel lasts as long as its chain of products,
+// 12 us at n = 16 and 28 us at n = 25; the split of a product over lanes takes 8
+// and 15 us, but a multiply-add costs it several LDS reads.  N = 32 without it
+// 295 us, with a limit of 8, 32, 128, 256, 512 parents 261, 244, 237, 234, 229 us;
+// N = 28 163, 136, 125, 117, 112, 113 us; a batch of N = 10 .. 36 20.5 ms with any
+// of them, 21.3 and 22.9 ms with 4096 and 16384.
+constexpr uint64_t kTopParents = 256;
+
 hipError_t launch_tree_elim(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count,
                             hipStream_t st) {
     const int n = mp.n, T = n - level - 1;
     if (count == 0) return hipSuccess;
     if (n < 1 || n > kTreeMaxPairs || T < 0) return hipErrorInvalidValue;
-    // couplings of the few nodes near the root over several wavefronts, until
-    // about two per SIMD are in flight
+    if (count <= kTopParents || T > kElimPairs) return launch_tree_top_elim<treelane::F64>(mp, level, g0, count, st);
+    if (count > (uint64_t)INT32_MAX) return hipErrorInvalidValue;
+    // couplings of larger nodes over several wavefronts, until about two per SIMD
+    // are in flight
     const int rounds = (tree_entries(T) - 1 + 63) / 64;
     const int slices = (int)std::max<uint64_t>(1, std::min<uint64_t>(rounds, 2048 / count));
     const TreeElimArgs a{&mp, &sh, level, g0, count, slices};
