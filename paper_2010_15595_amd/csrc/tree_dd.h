@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(treedd::kThreads) tree_dd_leaf_kernel(TreeMap 
     cdd *fs = f + grp * (P + 1), *es = e + grp * (P + 1);
     const bool mine = k <= n;
     if (mine) {
-        const cdd p = b.base[(k - 1) * b.stride], q = b.base[k * b.stride + 1];
+        const cdd p = b.base[k * b.stride], q = b.base[k * b.stride + 1];
         fs[k] = cdd_mul_d(cdd_add(p, cdd_mul_d(q, (double)k)), 0.5);
     }
     if (k == 1) es[0] = cdd_make(1.0, 0.0);

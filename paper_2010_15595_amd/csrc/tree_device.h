@@ -29,8 +29,9 @@
 // coupling of vertices j and k, vertex 0 being the border, vertices 2i+1 and
 // 2i+2 pair i.  Entry 1, the border with itself, is held times x (n + 1
 // coefficients, the first zero): it alone takes its products without the
-// factor x of the others, and so all entries are updated alike.  The last pair is eliminated first, so an exclude child's list
-// is a prefix of its parent's.
+// factor x of the others, and so all entries are updated alike.  Entry 0 is held
+// in coefficients 1..n.  The last pair is eliminated first, so an exclude
+// child's list is a prefix of its parent's.
 //
 // Work split: one lane per series product, all coefficients of the operands in
 // registers (n^2 / 2 complex multiply-adds from one 16 n byte load of one
@@ -123,22 +124,23 @@ struct LdsSeries {
 // k / 2 and complete after step k - 1.  Operands are read kAhead steps ahead, in
 // source order (left to itself the compiler moves all reads to the front and
 // spills).
-constexpr int kAhead = 4;
+template <int NN>
+constexpr int kAhead = NN < 28 ? 4 : 3;  // n = 28 spills with 4
 
 // acc_k += sum_(i + j = k - 1) y_i m_j for k <= K (K <= NN); Y, M: get(k), called in order.
 template <int NN, int K, class Y, class M>
 __device__ __forceinline__ void conv(double2 (&acc)[NN + 1], Y ys, M ms) {
     double2 y[NN], m[NN];
 #pragma unroll
-    for (int d = 0; d < kAhead && d < K; ++d) {
+    for (int d = 0; d < kAhead<NN> && d < K; ++d) {
         y[d] = ys.get(d);
         m[d] = ms.get(d);
     }
 #pragma unroll
     for (int d = 0; d < K; ++d) {
-        if (d + kAhead < K) {
-            y[d + kAhead] = ys.get(d + kAhead);
-            m[d + kAhead] = ms.get(d + kAhead);
+        if (d + kAhead<NN> < K) {
+            y[d + kAhead<NN>] = ys.get(d + kAhead<NN>);
+            m[d + kAhead<NN>] = ms.get(d + kAhead<NN>);
         }
 #pragma unroll
         for (int i = 0; i <= d; ++i) {
@@ -159,7 +161,7 @@ __device__ __forceinline__ void conv_stream(Y ys, M ms, In in, Out out) {
     acc[0] = in.get(0);
     constexpr int K = NN - 1;
 #pragma unroll
-    for (int d = 0; d < kAhead && d < K; ++d) {
+    for (int d = 0; d < kAhead<NN> && d < K; ++d) {
         y[d] = ys.get(d);
         m[d] = ms.get(d);
         if (d > 0) acc[2 * d] = 2 * d < NN ? in.get(2 * d) : acc[0];
@@ -168,7 +170,7 @@ __device__ __forceinline__ void conv_stream(Y ys, M ms, In in, Out out) {
     out.put(0, acc[0]);
 #pragma unroll
     for (int d = 0; d < K; ++d) {
-        const int q = d + kAhead;
+        const int q = d + kAhead<NN>;
         if (q < K) {
             y[q] = ys.get(q);
             m[q] = ms.get(q);
@@ -199,14 +201,14 @@ __device__ __forceinline__ void solve(U us, R rs, double scale, F done) {
     };
     y[0] = rs.get(0);
 #pragma unroll
-    for (int d = 0; d < kAhead; ++d) {
+    for (int d = 0; d < kAhead<NN>; ++d) {
         if (d + 1 < NN) u[d] = us.get(d);
         if (d > 0 && 2 * d < NN) rhs(2 * d);
         if (2 * d + 1 < NN) rhs(2 * d + 1);
     }
 #pragma unroll
     for (int d = 0; d < NN; ++d) {
-        const int q = d + kAhead;
+        const int q = d + kAhead<NN>;
         if (q + 1 < NN) u[q] = us.get(q);
         if (2 * q < NN) rhs(2 * q);
         if (2 * q + 1 < NN) rhs(2 * q + 1);
@@ -219,6 +221,69 @@ __device__ __forceinline__ void solve(U us, R rs, double scale, F done) {
             }
         }
         if (d + 1 < NN) keep_order(y[d + 1], y[2 * d + 1 < NN ? 2 * d + 1 : NN - 1]);
+    }
+}
+
+// Value of the even (P = 0) or odd (P = 1) lane of the caller's pair of lanes.
+template <int P>
+__device__ __forceinline__ double pair_bcast(double x) {
+    const long long b = __double_as_longlong(x);
+    constexpr int ctrl = P ? 0xF5 : 0xA0;  // quad_perm 1 1 3 3, 0 0 2 2
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, ctrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// The same products on a pair of lanes, each with the outputs of its parity p
+// (half of the multiply-adds): out_k = in_k + sum_(i + j = k - 1) y_i m_j for k =
+// 2t + p.  With m'_j = m_(j-1+p), m'_0 = 0 for p = 0, output t takes the products
+// with i + j = 2t on either lane.  SOLVE: y is the output itself (out = in / (1 -
+// x m)), handed over between the lanes.  Every in_k is read before out_k is
+// written, and m_k, too.  in_k is scaled by 1 + scale k.  For odd NN the odd lane
+// also reads and writes coefficient NN, with no meaning.  In tree_sub_kernel<25> a
+// solve takes 5400 cycles this way and 7900 on single lanes, an update of v's row
+// 4300 and 6650 (5200 are the multiply-adds of a whole product).
+template <int NN, bool SOLVE, class Y, class M, class In, class Out>
+__device__ __forceinline__ void half_products(int p, double scale, Y ys, M ms, In in, Out out) {
+    constexpr int H = (NN + 1) / 2, D = 2 * H - 1, A = kAhead<NN>;
+    double2 y[D], m[D], acc[H];
+    auto load_m = [&](int d) { m[d] = ms.get(d == 0 ? 0 : d - 1 + p); };
+    auto load_in = [&](int t) {
+        const double2 r = in.get(2 * t + p);
+        if (SOLVE) {
+            const double f = fma(scale, (double)(2 * t + p), 1.0);
+            acc[t] = make_double2(r.x * f, r.y * f);
+        } else {
+            acc[t] = r;
+        }
+    };
+    load_m(0);
+    m[0] = make_double2(p ? m[0].x : 0.0, p ? m[0].y : 0.0);
+#pragma unroll
+    for (int d = 0; d < A; ++d) {
+        if (d + 1 < D) load_m(d + 1);
+        if (!SOLVE && d < D) y[d] = ys.get(d);
+        if (d < H) load_in(d);
+    }
+    // step d: y_d with m'_0..m'_(d+1) and m'_(d+1) with the lower y, so that out_(d+1)
+    // is complete after it on either lane
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        const int q = d + A;
+        if (q + 1 < D) load_m(q + 1);
+        if (!SOLVE && q < D) y[q] = ys.get(q);
+        if (q < H) load_in(q);
+        if (SOLVE)
+            y[d] = (d & 1) ? make_double2(pair_bcast<1>(acc[d / 2].x), pair_bcast<1>(acc[d / 2].y))
+                           : make_double2(pair_bcast<0>(acc[d / 2].x), pair_bcast<0>(acc[d / 2].y));
+#pragma unroll
+        for (int i = 0; i <= d; i += 2) {
+            const int j = i + (d & 1), l = i + ((d + 1) & 1);
+            if (l < d && l + d + 1 < D) acc[(l + d + 1) / 2] = mac(y[l], m[d + 1], acc[(l + d + 1) / 2]);
+            if (d + j < D) acc[(d + j) / 2] = mac(y[d], m[j], acc[(d + j) / 2]);
+        }
+        if (!(d & 1)) out.put(d + p, acc[d / 2]);
+        keep_order(acc[(d + 1) / 2 < H ? (d + 1) / 2 : H - 1], acc[d < H ? d : H - 1]);
     }
 }
 
@@ -264,8 +329,8 @@ __device__ __forceinline__ void elim_pair(Block pb, Block cb, double2* lds, int 
         order_wave();
     }
     if (d0 == 0 && lane < NN) {
-        const double2 p = pb.base[lane * pb.stride], u = tmp(PLANE - 2).get(lane), v = tmp(PLANE - 1).get(lane);
-        cb.base[lane * cb.stride] = make_double2(p.x + u.x + v.x, p.y + u.y + v.y);
+        const double2 p = pb.base[(lane + 1) * pb.stride], u = tmp(PLANE - 2).get(lane), v = tmp(PLANE - 1).get(lane);
+        cb.base[(lane + 1) * cb.stride] = make_double2(p.x + u.x + v.x, p.y + u.y + v.y);
     }
     // the child's couplings m_jk + x y_j m_uk + x z_j m_vk; the border's own is
     // held times x, so that it takes the same products
@@ -358,8 +423,11 @@ __global__ void __launch_bounds__(64, (NN <= 25 ? 2 : 1)) tree_elim_kernel(TreeM
 
 // LDS series per parent while a pair is eliminated, T pairs left after it, in
 // tree_sub_kernel: rows u (W + 1, y_v over m_uu) and v (W + 2, updated in
-// place) of the pair's vertices and y (W, then z), W = 2T + 1.
-constexpr int kTreeSlots = 96;  // 2^(4-T) parents of 6T + 6 series, T = 0..4
+// place) of the pair's vertices and y (W, then z), W = 2T + 1, and where a solve
+// runs on pairs of lanes in both phases the power sums of u.
+__host__ __device__ constexpr int tree_slots(int T) { return T >= 2 ? 6 * T + 7 : 6 * T + 6; }
+constexpr int kTreeOne = 96;  // 2^(4-T) parents, T = 0..4; the series 1 after them
+constexpr int kTreeSlots = 97;
 __host__ __device__ constexpr int tree_lanes(int T) { return T == 0 ? 4 : tree_entries(T); }
 
 // The subtree of up to kTreeDepth pairs below nodes g0 + blockIdx.x of `level`:
@@ -373,7 +441,10 @@ __host__ __device__ constexpr int tree_lanes(int T) { return T == 0 ? 4 : tree_e
 // (With the entries of each level in device memory instead, 134 KB a wavefront
 // at n = 25, the kernel moved 150 GB at N = 44 and kept the VALU 33% busy.)
 // Between levels the entries change lanes through one 2 KB LDS line per
-// coefficient.
+// coefficient.  Bound by FP64 issue: of the 95 us of 1024 nodes at n = 25 (112
+// with all products on single lanes) the couplings take 31%, on 45 to 60 of 64
+// lanes, the first solves 20%, the second ones 13%, the rows of v 11%, the changes
+// of lanes 9%, which the LDS bandwidth bounds, the leaves 5%.
 template <int NN>
 __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
     tree_sub_kernel(TreeMap mp, TreeShard sh, int level, uint64_t g0, double* __restrict__ records) {
@@ -392,6 +463,7 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
         return;
     }
     double2 sa[NN + 1], sb[NN + 1];
+    if (lane < NN) row(kTreeOne).put(lane, make_double2(lane == 0 ? 1.0 : 0.0, 0.0));
     {
         // the node's prefix to sa, its last pair's rows to LDS
         const tree::Block root = tree::node_block(mp, level, g);
@@ -417,12 +489,12 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
             const int Lp = tree_lanes(T + 1), Ep = tree_entries(T + 1);
             const int cp = lane / Lp, ep = lane - cp * Lp;
             const bool rowp = cp < P / 2 && ep >= E && ep < Ep;
-            const int slot = 2 * cp * (6 * T + 6) + ep - E;
+            const int slot = 2 * cp * tree_slots(T) + ep - E;
             if (rowp) {
 #pragma unroll
                 for (int k = 0; k < NN; ++k) {
                     row(slot).put(k, sa[k]);
-                    row(slot + 6 * T + 6).put(k, sb[k]);
+                    row(slot + tree_slots(T)).put(k, sb[k]);
                 }
             }
             const int from = on && x < E ? ((c >> 1) * Lp + x + 64 * (c & 1)) : lane;
@@ -438,7 +510,7 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
 #pragma unroll
         for (int k = 0; k <= NN; ++k) sb[k] = sa[k];
         tree::order_wave();
-        const int tb = c * (6 * T + 6);
+        const int tb = c * tree_slots(T);
         const int xc = max(x - 1, 0);  // coupling (j, k0)
         int j = (int)((__builtin_sqrtf(8.0f * (float)xc + 1.0f) - 1.0f) * 0.5f);
         if (tree_tri(j + 1, 0) <= xc) ++j;
@@ -447,32 +519,46 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
 #pragma unroll 1
         for (int ph = 0; ph < 2; ++ph) {
             // phase 0: y_j = m_uj / (1 - x m_uu) for every other vertex j < W and for
-            // v (j = W); phase 1: z_j likewise with the updated row of v; x = 0: the
-            // power sums
-            if (on && x <= (ph == 0 ? W + 1 : W)) {
-                const int su = tb + (ph == 0 ? W : 2 * W + 2);
-                const int sr = x == 0 ? su : (x == W + 1 ? tb + 2 * W + 1 : tb + x - 1 + (ph == 0 ? 0 : W + 1));
-                const int so = x == W + 1 ? W : 2 * W + 2 + x;
-                double2 y[NN];
-                tree::solve<NN>(row(su), row(sr), x == 0 ? 1.0 : 0.0, [&](int k, double2 v) { y[k] = v; });
-                tree::order_wave();
-                if (x == 0) {
+            // v (j = W); phase 1: z_j likewise with the updated row of v; row x = 0:
+            // the power sums.  On pairs of lanes where 32 rows do.
+            const int pl = lane & 1, rows = W + 2 - ph;
+            if (ph == 0 && T < 2) {
+                if (on && x <= W + 1) {
+                    const int su = tb + W, sr = x == 0 ? su : (x == W + 1 ? tb + 2 * W + 1 : tb + x - 1);
+                    const int so = x == W + 1 ? W : 2 * W + 2 + x;
+                    double2 y[NN];
+                    tree::solve<NN>(row(su), row(sr), x == 0 ? 1.0 : 0.0, [&](int k, double2 v) { y[k] = v; });
+                    tree::order_wave();
+                    if (x == 0) {
 #pragma unroll
-                    for (int k = 0; k < NN; ++k) sb[k] = make_double2(sb[k].x + y[k].x, sb[k].y + y[k].y);
-                } else {
+                        for (int k = 0; k < NN; ++k) sb[k + 1] = make_double2(sb[k + 1].x + y[k].x, sb[k + 1].y + y[k].y);
+                    } else {
 #pragma unroll
-                    for (int k = 0; k < NN; ++k) row(tb + so).put(k, y[k]);
+                        for (int k = 0; k < NN; ++k) row(tb + so).put(k, y[k]);
+                    }
+                }
+            } else {
+                const int cr = (lane >> 1) / rows, xr = (lane >> 1) - cr * rows, tr = cr * tree_slots(T);
+                if (cr < P) {
+                    const int su = tr + (ph == 0 ? W : 2 * W + 2);
+                    const int sr = xr == 0 ? su : (xr == W + 1 ? tr + 2 * W + 1 : tr + xr - 1 + (ph == 0 ? 0 : W + 1));
+                    const int so = xr == 0 ? (ph == 0 ? 3 * W + 3 : W) : (xr == W + 1 ? W : 2 * W + 2 + xr);
+                    tree::half_products<NN, true>(pl, xr == 0 ? 1.0 : 0.0, row(su), row(su), row(sr), row(tr + so));
                 }
             }
             tree::order_wave();
-            // the include child's couplings: m_jk + x y_j m_uk, then + x z_j m_vk
-            if (on && x >= 1 && x < E)
-                tree::conv<NN, NN>(sb, row(tb + 2 * W + 3 + j), row(tb + k0 + (ph == 0 ? 0 : W + 1)));
+            // the include child's couplings: m_jk + x y_j m_uk, then + x z_j m_vk; its
+            // power sums (x = 0) are those of u and v times 1
+            if (on && x < E && (x > 0 || T >= 2 || ph == 1)) {
+                const int sy = x == 0 ? (ph == 0 ? 3 * W + 3 : W) : 2 * W + 3 + j;
+                tree::conv<NN, NN>(sb, row(tb + sy), row(x == 0 ? kTreeOne : tb + k0 + (ph == 0 ? 0 : W + 1)));
+            }
             if (ph == 0) {
                 // row of v: m_vj + x y_v m_uj, and m_vv + x y_v m_uv
-                if (on && x >= 1 && x <= W + 1) {
-                    const tree::LdsSeries<PL> rv = row(tb + (x <= W ? W + x : 2 * W + 2));
-                    tree::conv_stream<NN>(row(tb + W), row(tb + (x <= W ? x - 1 : 2 * W + 1)), rv, rv);
+                const int cr = (lane >> 1) / (W + 1), xr = (lane >> 1) - cr * (W + 1), tr = cr * tree_slots(T);
+                if (cr < P) {
+                    const tree::LdsSeries<PL> rv = row(tr + (xr < W ? W + 1 + xr : 2 * W + 2));
+                    tree::half_products<NN, false>(pl, 0.0, row(tr + W), row(tr + (xr < W ? xr : 2 * W + 1)), rv, rv);
                 }
                 tree::order_wave();
             }
@@ -486,9 +572,8 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
         if (x < 2) {
 #pragma unroll
             for (int k = 0; k < NN; ++k) {
-                const double2 a0 = sa[k], a1 = sa[k + 1], b0 = sb[k], b1 = sb[k + 1];
-                lds[k * PL + sl] = make_double2(x ? a1.x : a0.x, x ? a1.y : a0.y);
-                lds[k * PL + sl + 2] = make_double2(x ? b1.x : b0.x, x ? b1.y : b0.y);
+                lds[k * PL + sl] = sa[k + 1];
+                lds[k * PL + sl + 2] = sb[k + 1];
             }
         }
         tree::order_wave();

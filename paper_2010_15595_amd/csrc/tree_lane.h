@@ -163,7 +163,7 @@ __global__ void __launch_bounds__(treelane::kThreads) tree_lane_elim_kernel(Tree
     for (int t = tid; t < nodes * n; t += NT) {
         const int c = t / n, k = t - c * n;
         const Block<V> pb = parent(c), cb = child(c);
-        cb.base[k * cb.stride] = AR::add(pb.base[k * pb.stride], AR::add(p_at(c, 0, k), p_at(c, 1, k)));
+        cb.base[(k + 1) * cb.stride] = AR::add(pb.base[(k + 1) * pb.stride], AR::add(p_at(c, 0, k), p_at(c, 1, k)));
     }
     // the children's couplings m_jk + x y_j m_uk + x z_j m_vk (the border's own held
     // times x, n + 1 coefficients)
@@ -294,8 +294,8 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
             constexpr int i = decltype(I)::value;
             if (i < n - 1) {
                 const V y = AR::template bcast<(i & 15)>(AR::value(i < 16 ? c0 : c1));
-                if (i < 15) AR::mac(c0, y, s[-i]);
-                if (WIDE) AR::mac(c1, y, s[16 - i]);
+                if (i < 15) AR::mac(c0, s[-i], y);
+                if (WIDE) AR::mac(c1, s[16 - i], y);
             }
         });
         a0 = AR::value(c0);
@@ -311,8 +311,8 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
             p0 = a0;
             p1 = a1;
         } else if (r == W + 1 && blockIdx.y == 0) {
-            if (lo) cb.base[kl * E] = AR::add(pb.base[kl * pb.stride], AR::add(p0, a0));
-            if (hi) cb.base[(kl + 16) * E] = AR::add(pb.base[(kl + 16) * pb.stride], AR::add(p1, a1));
+            if (lo) cb.base[(kl + 1) * E] = AR::add(pb.base[(kl + 1) * pb.stride], AR::add(p0, a0));
+            if (hi) cb.base[(kl + 17) * E] = AR::add(pb.base[(kl + 17) * pb.stride], AR::add(p1, a1));
         }
         __syncthreads();
         if (ph == 0) {
@@ -323,8 +323,8 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
                 constexpr int i = decltype(I)::value;
                 if (i < n - 1) {
                     const V y = AR::template bcast<(i & 15)>(i < 16 ? u0 : u1);
-                    if (i < 15) AR::mac(d0, y, q[-i]);
-                    if (WIDE) AR::mac(d1, y, q[16 - i]);
+                    if (i < 15) AR::mac(d0, q[-i], y);
+                    if (WIDE) AR::mac(d1, q[16 - i], y);
                 }
             });
             v0 = AR::value(d0);
