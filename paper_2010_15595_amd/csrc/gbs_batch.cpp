@@ -62,7 +62,7 @@ namespace gbs_host {
 
 void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, int64_t tile_subsets,
                     int64_t round_bytes, bool tile_offsets, BatchSchedule& S) {
-    S = BatchSchedule();
+    S.reset();
     S.count = (int)dims.size();
     S.fp32 = fp32;
     S.tile_subsets = tile_subsets;
@@ -74,33 +74,53 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
     const int nitems = S.count;
 
     bool route[gbs::kMaxPairs + 1];  // items of n pairs run on the subset tree
-    for (int n = 0; n <= gbs::kMaxPairs; ++n) route[n] = tree_route(c, n, fp32);
-
-    // items (flop yardstick per dimension computed once)
-    double flops_of[GBS_MAX_DIM + 1];
-    bool have_flops[GBS_MAX_DIM + 1] = {};
+    for (int n = 1; n <= gbs::kMaxPairs; ++n) route[n] = tree_route(c, n, fp32);
+    route[0] = !fp32;  // no kernel but the one that writes the result
+    // counted by dimension first: tens of thousands of items have a few dozen
+    int64_t of_dim[GBS_MAX_DIM + 1] = {}, on_tree[gbs::kMaxPairs + 1] = {};
+    for (int N : dims) ++of_dim[N];
+    for (int N = 0; N <= GBS_MAX_DIM; ++N) {
+        if (of_dim[N] == 0) continue;
+        const int n = (N + 1) / 2;
+        if (route[n])
+            on_tree[n] += of_dim[N];
+        else
+            S.tiled = true;
+        S.max_n = n;
+        S.subset_terms += of_dim[N] << n;
+        S.flops += (double)of_dim[N] * gbs_yardstick_flops(N);
+    }
+    // tree groups by n, most pairs first, each a range of tlist; next[n]: its next entry
+    int64_t next[gbs::kMaxPairs + 1];
+    {
+        int64_t at = 0;
+        for (int n = gbs::kMaxPairs; n >= 0; --n) {
+            next[n] = at;
+            at += on_tree[n];
+        }
+        S.tlist.resize((size_t)at);
+    }
     S.in_off.resize(nitems);
-    S.a0_off.resize(nitems);
-    S.d_off.resize(nitems);
-    S.npair.resize(nitems);
+    if (S.tiled) {
+        S.a0_off.resize(nitems);
+        S.d_off.resize(nitems);
+        S.npair.resize(nitems);
+    }
     for (int i = 0; i < nitems; ++i) {
-        const int N = dims[i], Np = N + (N & 1);
-        S.npair[i] = Np / 2;
+        const int N = dims[i], n = (N + 1) / 2;
         S.in_off[i] = S.in_elems;
+        S.in_elems += (int64_t)N * N;
+        if (route[n]) S.tlist[(size_t)next[n]++] = i;
+    }
+    for (int i = 0; S.tiled && i < nitems; ++i) {
+        const int Np = dims[i] + (dims[i] & 1);
+        S.npair[i] = Np / 2;
         S.a0_off[i] = route[Np / 2] ? -1 : S.a0_elems;
         S.d_off[i] = S.d_elems;
-        S.in_elems += (int64_t)N * N;
         if (!route[Np / 2]) {
             S.a0_elems += (int64_t)Np * Np;
             S.d_elems += Np;
         }
-        S.max_n = std::max(S.max_n, Np / 2);
-        S.subset_terms += (int64_t)1 << (Np / 2);
-        if (!have_flops[N]) {
-            flops_of[N] = gbs_yardstick_flops(N);
-            have_flops[N] = true;
-        }
-        S.flops += flops_of[N];
     }
 
     // tiles: (item, s, rank range); series blocks and partial ranges per item
@@ -115,14 +135,9 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
     int small_pairs = gbs::kSmallPairs;
     if (const char* e = std::getenv("GBS_SMALL_PAIRS")) small_pairs = std::max(0, std::min(gbs::kSmallPairs, atoi(e)));
     std::vector<HostTile> ht;
-    std::vector<int> by_pairs[gbs::kMaxPairs + 1];  // items on the subset tree
-    for (int i = 0; i < nitems; ++i) {
+    for (int i = 0; S.tiled && i < nitems; ++i) {
         const int n = S.npair[i];
-        if (route[n]) {
-            by_pairs[n].push_back(i);
-            continue;
-        }
-        S.tiled = true;
+        if (route[n]) continue;
         if (!fp32 && n >= 1 && n <= small_pairs) {
             S.small.push_back(i);
             continue;
@@ -149,14 +164,14 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
     }
     // groups of equal n, most work first, over the branches in turn
     for (int n = gbs::kMaxPairs; n >= 1; --n) {
-        if (by_pairs[n].empty()) continue;
+        if (on_tree[n] == 0) continue;
         TreeGroup g;
-        g.begin = (int)S.tlist.size();
-        g.count = (int)by_pairs[n].size();
-        S.tlist.insert(S.tlist.end(), by_pairs[n].begin(), by_pairs[n].end());
+        g.begin = (int)(next[n] - on_tree[n]);
+        g.count = (int)on_tree[n];
         tree_sched(n, (uint64_t)g.count, kBatchTreeBudget, g.S);
         S.tree.push_back(g);
     }
+    S.empty = (int)on_tree[0];
     std::stable_sort(S.tree.begin(), S.tree.end(), [](const TreeGroup& a, const TreeGroup& b) {
         return (double)a.count * std::ldexp((double)(a.S.n * a.S.n), a.S.n) >
                (double)b.count * std::ldexp((double)(b.S.n * b.S.n), b.S.n);
@@ -175,6 +190,7 @@ void batch_schedule(const DevCtx* c, const std::vector<int>& dims, bool fp32, in
         S.small.clear();
         for (int n = gbs::kSmallPairs; n >= 1; --n) S.small.insert(S.small.end(), by_n[n].begin(), by_n[n].end());
     }
+    if (!S.tiled) return;
     // partials: per item contiguous, in (item, s, rank) order
     S.pbeg.assign(nitems + 1, 0);
     std::vector<int64_t> tile_pidx(ht.size());
@@ -266,6 +282,10 @@ gbs_status batch_enqueue(DevCtx* c, const BatchSchedule& S, const BatchDev& d, h
     if (S.tiled) {
         HIP_TRY(gbs::launch_fill_u32(d.counters, (int)std::max<size_t>(1, S.cp.size()), cs));
         HIP_TRY(gbs::launch_batch_prep(d.mats, d.in_off, d.dims, d.items, nitems, cs));
+    }
+    if (S.empty > 0) {
+        HIP_TRY(gbs::launch_tree_items(d.tlist + (S.tlist.size() - (size_t)S.empty), S.empty, nullptr, 0, d.out, d.abs, cs));
+        if (tree_launches) ++*tree_launches;
     }
     std::vector<hipEvent_t> tree_joins;
     hipEvent_t ev_prep;
@@ -395,6 +415,7 @@ void plan_free(gbs_plan* p) {
 }
 
 std::vector<gbs::BatchItem> item_table(const BatchSchedule& S, double2* a0, double2* dv) {
+    if (!S.tiled) return {};
     std::vector<gbs::BatchItem> items(S.count);
     for (int i = 0; i < S.count; ++i)
         items[i] = gbs::BatchItem{S.a0_off[i] < 0 ? nullptr : a0 + S.a0_off[i], dv + S.d_off[i], 2 * S.npair[i],
@@ -442,7 +463,7 @@ gbs_status plan_build_into(DevCtx* c, const std::vector<int>& dims, bool fp32, i
         d.lbmap = static_cast<int4*>(tb);
         HIP_TRY(hipMemcpy(tb, c->lbmap, nl, hipMemcpyDeviceToDevice));
     }
-    if ((st = dmalloc((void**)&d.partials, sizeof(double) * 5 * (size_t)std::max<int64_t>(1, S.pbeg[nitems]), &B)) !=
+    if ((st = dmalloc((void**)&d.partials, sizeof(double) * 5 * (size_t)std::max<int64_t>(1, S.partials()), &B)) !=
         GBS_OK)
         return st;
     if ((st = dmalloc((void**)&d.counters, sizeof(unsigned) * std::max<size_t>(1, S.cp.size()), &B)) != GBS_OK)
@@ -550,14 +571,14 @@ gbs_status runner_run(BatchRunner* r, const BatchSchedule& S, const double2* mat
     // the pinned staging and the buffers may be reused only once the previous run has finished with them
     if (r->uploaded) HIP_TRY(hipEventSynchronize(r->upload_done));
     auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    const size_t n_items = sizeof(gbs::BatchItem) * S.count, n_inoff = sizeof(int64_t) * S.in_off.size(),
+    const size_t n_items = S.tiled ? sizeof(gbs::BatchItem) * S.count : 0, n_inoff = sizeof(int64_t) * S.in_off.size(),
                  n_dims = sizeof(int) * S.dims.size(), n_tiles = sizeof(gbs::BatchTile) * S.tiles.size(),
                  n_sb = sizeof(gbs::SeriesBlock) * S.sblocks.size(), n_pbeg = sizeof(int64_t) * S.pbeg.size(),
                  n_small = sizeof(int) * S.small.size(), n_tlist = sizeof(int) * S.tlist.size();
     const size_t o_items = 0, o_inoff = align(o_items + n_items), o_dims = align(o_inoff + n_inoff),
                  o_tiles = align(o_dims + n_dims), o_sb = align(o_tiles + n_tiles), o_pbeg = align(o_sb + n_sb),
                  o_small = align(o_pbeg + n_pbeg), o_tlist = align(o_small + n_small), total = align(o_tlist + n_tlist);
-    const size_t npart = 5 * (size_t)std::max<int64_t>(1, S.pbeg[S.count]);
+    const size_t npart = 5 * (size_t)std::max<int64_t>(1, S.partials());
     bool tree_grow = r->trec_cap < 40 * (size_t)S.tree_records;
     for (int b = 0; b < kBatchBranches; ++b)
         tree_grow = tree_grow || r->tarena_cap[b] < S.tree_arena[b] || r->tnodes_cap[b] < 40 * (size_t)S.tree_nodes[b];
@@ -598,12 +619,12 @@ gbs_status runner_run(BatchRunner* r, const BatchSchedule& S, const double2* mat
     }
     const std::vector<gbs::BatchItem> items = item_table(S, (double2*)r->a0, (double2*)r->dv);
     char* h = r->host_meta;
-    std::memcpy(h + o_items, items.data(), n_items);
+    if (n_items) std::memcpy(h + o_items, items.data(), n_items);
     std::memcpy(h + o_inoff, S.in_off.data(), n_inoff);
     std::memcpy(h + o_dims, S.dims.data(), n_dims);
     if (n_tiles) std::memcpy(h + o_tiles, S.tiles.data(), n_tiles);
     if (n_sb) std::memcpy(h + o_sb, S.sblocks.data(), n_sb);
-    std::memcpy(h + o_pbeg, S.pbeg.data(), n_pbeg);
+    if (n_pbeg) std::memcpy(h + o_pbeg, S.pbeg.data(), n_pbeg);
     if (n_small) std::memcpy(h + o_small, S.small.data(), n_small);
     if (n_tlist) std::memcpy(h + o_tlist, S.tlist.data(), n_tlist);
     HIP_TRY(hipMemcpyAsync(r->meta, h, total, hipMemcpyHostToDevice, st));

@@ -200,8 +200,26 @@ struct BatchSchedule {
     size_t tree_arena[kBatchBranches] = {};
     uint64_t tree_nodes[kBatchBranches] = {};
     int64_t tree_records = 0;
-    bool tiled = false;                 // some item runs on tiles, as a small item or is empty
+    int empty = 0;                      // matrices of dimension 0, last in tlist
+    bool tiled = false;                 // some item runs on tiles or as a small item: only then npair, a0_off, d_off
+                                        // and pbeg are filled
     std::vector<int> small;             // FP64 items with 1 <= n <= kSmallPairs, largest n first: one wavefront each
+    int64_t partials() const { return pbeg.empty() ? 0 : pbeg.back(); }
+    // As new, with the per-item arrays' memory kept: a sampling chain schedules
+    // tens of thousands of items per step, and pages of fresh arrays cost it more
+    // than filling them.
+    void reset() {
+        BatchSchedule n;
+        std::vector<int>*kept[] = {&dims, &npair, &tlist, &small}, *to[] = {&n.dims, &n.npair, &n.tlist, &n.small};
+        std::vector<int64_t>*kept8[] = {&in_off, &a0_off, &d_off, &pbeg}, *to8[] = {&n.in_off, &n.a0_off, &n.d_off, &n.pbeg};
+        for (int i = 0; i < 4; ++i) {
+            kept[i]->clear();
+            to[i]->swap(*kept[i]);
+            kept8[i]->clear();
+            to8[i]->swap(*kept8[i]);
+        }
+        *this = std::move(n);
+    }
 };
 // tile_offsets: FP64 tiles keep C at the front tile offset of their m (one
 // persistent launch per offset); captured plans use it, the sampler's eagerly

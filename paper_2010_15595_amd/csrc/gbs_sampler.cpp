@@ -267,6 +267,7 @@ extern "C" gbs_status gbs_sample_pure(const gbs_z* Q, const gbs_z* alpha, int32_
     std::vector<double> ut((size_t)group * M);
     std::vector<int> P_tot(group), col(group), dims;
     std::vector<int> all_draws((size_t)group * M);
+    BatchSchedule S;
     for (int g0 = 0; g0 < nsamples; g0 += group) {
         const int G = std::min(group, nsamples - g0);
         ++groups;
@@ -292,13 +293,13 @@ extern "C" gbs_status gbs_sample_pure(const gbs_z* Q, const gbs_z* alpha, int32_
                 }
                 for (int j = 0; j < K1; ++j) dims[(size_t)b * K1 + j] = P_tot[b] + j;
             }
-            for (int n = 1; n <= (*std::max_element(dims.begin(), dims.end()) + 1) / 2; ++n)
+            const int top = *std::max_element(P_tot.begin(), P_tot.begin() + G) + cutoff;  // largest dimension
+            for (int n = 1; n <= (top + 1) / 2; ++n)
                 if ((st = maybe_tune(c, n)) != GBS_OK) return st;
-            BatchSchedule S;
             batch_schedule(c, dims, fp32, kTileSubsets, kRoundBytes, false, S);
             n_lhaf += S.count;
             n_terms += S.subset_terms;
-            for (int N : dims) max_dim = std::max(max_dim, N);
+            max_dim = std::max(max_dim, top);
             if ((st = ensure_buffer(&c->smats, &c->smats_cap, sizeof(double2) * std::max<int64_t>(1, S.in_elems), 1)) !=
                 GBS_OK)
                 return st;
