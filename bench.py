@@ -180,8 +180,8 @@ def batch_cpu_baseline(mats, seconds, one_thread_seconds):
 
 
 def roofline_from_profile(prof, steps, note):
-    """Roofline entry of the dominant per-subset kernel instance: its yardstick
-    flops per launch over its average launch duration (HIP event pairs on the
+    """Roofline entry of the dominant kernel instance: its operations (subset
+    tree) or yardstick flops (per-subset kernels) per launch over its average launch duration (HIP event pairs on the
     launch streams)."""
     achieved = prof["dominant_flops"] / (prof["dominant_ms"] / 1000.0) / 1e12 if prof["dominant_ms"] > 0 else None
     achieved_all = prof["charpoly_flops"] / (prof["charpoly_ms"] / 1000.0) / 1e12 if prof["charpoly_ms"] > 0 else None
@@ -286,7 +286,7 @@ def bench_batch(args, gbs):
     if not np.array_equal(out.cpu().numpy(), res):
         log("WARNING: eager (profiled) run differs from the graph replays")
     roof = roofline_from_profile(prof, args.roofline_steps,
-                                 "persistent per-subset kernel of one (lane grid, tile) class over the batch's tiles; "
+                                 "subtree or elimination kernel of one order over a group of the batch's items; "
                                  f"average launch from {args.roofline_steps} eager profiled run(s) of the captured "
                                  "schedule right after the timed graph replays, one launch at a time")
     roof["traffic"] = None
@@ -316,7 +316,8 @@ def bench_batch(args, gbs):
         },
         "subset_terms_per_s": terms_per_s,
         "yardstick_tflops": flops_per_s / 1e12,
-        "pct_fp64_peak": 100.0 * flops_per_s / (FP64_PEAK_TFLOPS * 1e12),
+        "pct_fp64_peak": 100.0 * prof["charpoly_flops"] / args.roofline_steps * args.steps / sec
+                         / (FP64_PEAK_TFLOPS * 1e12),
         "plan_seconds": plan_s,
         "plain_form": plain,
         "roofline": roof,
@@ -565,9 +566,10 @@ def fig3_sweep(args, gbs):
         prof = gbs.profile_read()
         gbs.profile_enable(False)
         flops = gbs.yardstick_flops(N)
-        roof = roofline_from_profile(prof, psteps, "gather + Householder Hessenberg + La Budde, one size class")
+        roof = roofline_from_profile(prof, psteps, "subtree kernel, 32 subsets per wavefront")
         row = {"fp64_seconds": sec, "fp64_lhaf_per_s": 1.0 / sec, "subset_terms_per_s": float(1 << n) / sec,
-               "pct_fp64_peak": 100.0 * flops / sec / (FP64_PEAK_TFLOPS * 1e12),
+               "pct_fp64_peak": 100.0 * prof["charpoly_flops"] / psteps / sec / (FP64_PEAK_TFLOPS * 1e12),
+               "yardstick_tflops": flops / sec / 1e12,
                "dominant_kernel": roof["kernel"], "dominant_frac": roof["frac"],
                "paper_seconds": paper.get(N), "speedup_vs_paper": paper[N] / sec if N in paper else None,
                "steps": steps}
@@ -805,12 +807,11 @@ def main():
         log("WARNING: result changed between steps (non-deterministic)")
     sec = gpu_ms / 1000.0
     lhaf_per_s = args.steps / sec
-    # roofline of the dominant per-subset kernel instance: its algorithmic flops per
-    # launch over its average launch duration (HIP events on the launch stream)
+    # roofline of the dominant kernel instance: its operations per launch over its average launch duration (HIP events on the launch stream)
     achieved = prof["dominant_flops"] / (prof["dominant_ms"] / 1000.0) / 1e12 if prof["dominant_ms"] > 0 else None
     achieved_all = prof["charpoly_flops"] / (prof["charpoly_ms"] / 1000.0) / 1e12 if prof["charpoly_ms"] > 0 else None
     log(f"{args.steps} steps in {gpu_ms:.1f} ms (wall {wall * 1e3:.1f} ms): {lhaf_per_s:.4f} lhaf/s, "
-        f"{terms * lhaf_per_s:.4e} subset-terms/s; charpoly kernels {prof['charpoly_ms']:.1f} ms over "
+        f"{terms * lhaf_per_s:.4e} subset-terms/s; subset kernels {prof['charpoly_ms']:.1f} ms over "
         f"{prof['charpoly_launches']} launches, series {prof['series_ms']:.1f} ms, reduce {prof['reduce_ms']:.2f} ms")
     log(f"lhaf = {val:.12e}, sum|t_S| = {abs_sum:.4e}, kappa = {abs_sum / abs(val):.3e}")
 
@@ -838,13 +839,17 @@ def main():
         },
         "subset_terms_per_s": terms * lhaf_per_s,
         "yardstick_flops_per_lhaf": flops,
-        "pct_fp64_peak": 100.0 * flops * lhaf_per_s / (FP64_PEAK_TFLOPS * 1e12),
+        # the yardstick is the paper's formulation; the operations are those of the kernels run
+        "operations_per_lhaf": prof["charpoly_flops"] / args.steps,
+        "pct_fp64_peak": 100.0 * prof["charpoly_flops"] / args.steps * lhaf_per_s / (FP64_PEAK_TFLOPS * 1e12),
         "roofline": {
             "bound": "alu",
             "kernel": prof["dominant_kernel"],
-            "kernel_note": ("one workgroup per subset, double-double; achieved counts FP64-yardstick flops, each dd "
-                            "operation costs 10-30 FP64 instructions" if args.precision == "dd" else
-                            "gather + Householder Hessenberg + La Budde of the subsets of one size class"),
+            "kernel_note": {"dd": "one include child of the subset tree; each dd multiply-add counts as one but takes 12 "
+                                  "FP64 instructions per real product",
+                            "fp64": "subtree of 5 pairs (32 subsets) per wavefront, series products in registers",
+                            "fp32comp": "gather + Householder Hessenberg + La Budde of the subsets of one size "
+                                        "class"}[args.precision],
             "achieved": achieved,
             "peak": FP64_PEAK_TFLOPS,
             "unit": "TFLOP/s",
@@ -853,10 +858,8 @@ def main():
             "traffic_unit": "HBM bytes per launch of the dominant instance (rocprofv3 FETCH_SIZE and WRITE_SIZE, "
                             "scaled by a plain copy)",
             # the path's own HBM input and output per loop hafnian: the N x N complex128
-            # matrix in, the complex result and sum |t_S| out (24 B); on top of that the
-            # per-subset kernel hands 2(n + 2) coefficients per subset to the series kernel
+            # matrix in, the complex result and sum |t_S| out (24 B)
             "algorithmic_bytes_per_lhaf": N * N * 16 + 24,
-            "handoff_bytes_per_subset": 2 * (n + 2) * 16,
             "flops_per_launch": prof["dominant_flops"] / max(1, prof["dominant_launches"]),
             "avg_launch_ms": prof["dominant_ms"] / max(1, prof["dominant_launches"]),
             "launches_per_step": prof["dominant_launches"] / args.steps,

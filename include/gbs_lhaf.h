@@ -36,8 +36,8 @@ extern "C" {
 #endif
 
 #define GBS_MAX_DIM 64
-/* Batch plans and the sampling chain run only the register-tile kernels, whose
- * largest tile holds a 56 x 56 subset matrix without register spills. */
+/* Batch plans and the sampling chain stop where the register tiles and the
+ * subset tree do: a 56 x 56 subset matrix, 28 pairs, without register spills. */
 #define GBS_MAX_BATCH_DIM 56
 /* Size of the fixed per-device scratch array of gbs_lhaf_device_noalloc. */
 #define GBS_NOALLOC_SCRATCH_BYTES (32 << 20)
@@ -147,11 +147,11 @@ typedef enum {
 } gbs_charpoly;
 
 /* lhaf of an N x N symmetric matrix A (leading dim lda, diagonal = loop weights)
- * on the LDS-resident reference kernels (one workgroup per subset, the same
- * formulation as gbs_lhaf) with the characteristic polynomials from `method`:
- * for comparing the two methods in one framework.  prec GBS_FP64 (either
- * method, N <= 64) or GBS_DD (La Budde only, N <= 56; diag->lhaf_lo holds the
- * low part); GBS_E_UNSUPPORTED otherwise.  GBS_E_NONFINITE when a subset's QR
+ * on the LDS-resident reference kernels (one workgroup per subset, one
+ * characteristic polynomial each) with `method`: for comparing the two methods
+ * in one framework.  prec GBS_FP64 (either method, N <= 64) or GBS_DD
+ * (GBS_CHARPOLY_LABUDDE only, N <= 56: the sum of gbs_lhaf, bit for bit;
+ * diag->lhaf_lo holds the low part); GBS_E_UNSUPPORTED otherwise.  GBS_E_NONFINITE when a subset's QR
  * iteration needs more than 30 sweeps for one eigenvalue.  Host pointers;
  * synchronous; diag may be NULL. */
 gbs_status gbs_lhaf_method(const gbs_z *A, int32_t N, int64_t lda, gbs_precision prec, gbs_charpoly method,
@@ -207,7 +207,8 @@ gbs_status gbs_lhaf_device(const gbs_z *A_dev, int32_t N, gbs_precision prec, gb
  * stream as in gbs_lhaf_device (asynchronous, ordered on `stream`); GBS_FP64
  * or GBS_FP32_COMP (GBS_E_UNSUPPORTED for GBS_DD); 0 <= shard < nshards <=
  * GBS_MAX_SHARDS (GBS_E_ARG otherwise).  N = 0 puts its single term, 1, in
- * shard 0.  With nshards = 1 the combined result is bitwise that of
+ * shard 0.  A shard whose subsets touch more of the subset tree than the
+ * per-subset kernels would cost runs on those.  With nshards = 1 the combined result is bitwise that of
  * gbs_lhaf_device; with more, it agrees to rounding (the terms are grouped
  * differently). */
 gbs_status gbs_lhaf_device_shard(const gbs_z *A_dev, int32_t N, gbs_precision prec, int32_t shard,
@@ -227,7 +228,8 @@ gbs_status gbs_combine_partials(const double *partials, int32_t count, gbs_z *ou
  * fixed device array of GBS_NOALLOC_SCRATCH_BYTES (32 MiB) per device, which
  * the library holds until the process ends; it keeps the last call's
  * contents, and every value a call reads from it is written by that call
- * first.  gbs_init(device) must have been called for the current device
+ * first.  FP64 sums up to N = 56 run on the subset tree in pieces that fit the
+ * array.  gbs_init(device) must have been called for the current device
  * (GBS_E_ARG otherwise).  N <= GBS_MAX_DIM (GBS_E_TOO_LARGE above);
  * GBS_FP64 or GBS_FP32_COMP (GBS_E_UNSUPPORTED for GBS_DD).  Lane grids are
  * those of earlier tuning or gbs_set_layout, else the defaults.  All calls on
@@ -261,8 +263,10 @@ typedef struct {
  * (the conditional-sampling chain of the paper's Sec. III produces such
  * batches: many loop hafnians of uneven size).  The input of a run is the
  * packed concatenation of the matrices: item i is an N_i x N_i row-major
- * block (diagonal = loop weights) at element offset sum_{j<i} N_j^2.  The plan
- * splits every item's subset sum into tiles (runs of subsets of one size
+ * block (diagonal = loop weights) at element offset sum_{j<i} N_j^2.  GBS_FP64
+ * items whose number of pairs has no lane grid set (gbs_set_layout) are grouped
+ * by it and each group's subset trees are expanded together.  For the others the
+ * plan splits every item's subset sum into tiles (runs of subsets of one size
  * class), processes them with persistent per-subset kernels that take tiles
  * largest first from a device counter, then the series kernels and a
  * fixed-order compensated reduction per item; the whole schedule is captured
@@ -336,7 +340,9 @@ typedef enum {
 /* Use `layout` for subsets of size s (m = 2s vertices) whenever the loop
  * hafnian has n pairs; n = 0 applies to every n, s = 0 to every size the
  * grid can hold (other sizes keep their setting).  GBS_LAYOUT_DEFAULT clears
- * the setting.  GBS_E_ARG if s > 0 and the grid cannot hold m x m.  Affects
+ * the setting.  GBS_FP64 loop hafnians of up to 28 pairs run on the subset tree
+ * unless a grid is set for some size of theirs; set grids, GBS_FP32_COMP and
+ * larger orders use the per-subset kernel.  GBS_E_ARG if s > 0 and the grid cannot hold m x m.  Affects
  * the current device. */
 gbs_status gbs_set_layout(int32_t n, int32_t s, int32_t layout);
 

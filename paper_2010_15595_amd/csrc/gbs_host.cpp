@@ -466,6 +466,17 @@ bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid
     return true;
 }
 
+// FP64 operations of the tree's kernels: series products of n (n + 1) / 2 complex
+// multiply-adds.  An include child with T pairs left takes 4W + 4 of them for the
+// solves and rows of its pair (W = 2T + 1) and two per coupling; a leaf takes one.
+static double tree_flops(int n, double products) { return 4.0 * n * (n + 1) * products; }
+static double tree_child_products(int T) { return 4.0 * (2 * T + 1) + 4.0 + 2.0 * (gbs::tree_entries(T) - 1); }
+static double tree_sub_products(int T0) {
+    double p = std::ldexp(1.0, T0);
+    for (int T = 0; T < T0; ++T) p += std::ldexp(tree_child_products(T), T0 - 1 - T);
+    return p;
+}
+
 gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSource& src, const gbs::TreeShard* shard,
                         double* records, hipStream_t st, int* launches, bool prof) {
     gbs::TreeMap mp{};
@@ -474,7 +485,7 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
     for (int lv = 0; lv <= S.levels; ++lv) mp.off[lv] = S.off[lv] * (uint64_t)(S.n + 1);
     gbs::TreeShard none{};
     const gbs::TreeShard& sh = shard ? *shard : none;
-    const double flops = gbs_yardstick_flops(2 * S.n) / (double)(1ull << S.levels);
+    const double flops = tree_flops(S.n, tree_sub_products(S.n - S.levels));
     const double subsets = (double)(1ull << (S.n - S.levels));
     const std::string elim = "tree_elim_kernel<" + std::to_string(S.n) + ">",
                       sub = "tree_sub_kernel<" + std::to_string(S.n) + ">";
@@ -487,14 +498,16 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
     for (uint64_t r0 = 0; r0 < S.items; r0 += S.roots) {
         const uint64_t roots = std::min(S.roots, S.items - r0);
         for (uint64_t& w : mp.win) w = 0;
-        HIP_TRY(gbs::launch_tree_root(mp, src, r0, roots, st));
-        ++nl;
+        if (S.levels > 0) {
+            HIP_TRY(gbs::launch_tree_root(mp, src, r0, roots, st));
+            ++nl;
+        }
         // nodes [g0, g0 + count) of level lv, their entries in place
         std::function<gbs_status(int, uint64_t, uint64_t)> run = [&](int lv, uint64_t g0, uint64_t count) -> gbs_status {
             if (lv == S.levels) {
                 double* rec = (S.fold > 1) ? b.nodes : records + 5 * ((r0 << lv) + g0);
                 HIP_TRY(timed(flops * (double)count, subsets * (double)count, sub,
-                              [&] { return gbs::launch_tree_sub(mp, sh, lv, g0, count, rec, st); }));
+                              [&] { return gbs::launch_tree_sub(mp, sh, src, r0, lv, g0, count, rec, st); }));
                 if (S.fold == 1) return GBS_OK;
                 const uint64_t out = count / S.fold;
                 HIP_TRY(gbs::launch_records_fold(b.nodes, (int64_t)count, (int64_t)S.fold,
@@ -516,7 +529,7 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
             for (uint64_t q = 0; q < count; q += S.piece[lv]) {
                 const uint64_t len = std::min(S.piece[lv], count - q);
                 mp.win[lv + 1] = g0 + q;
-                HIP_TRY(timed(0.0, 0.0, elim, [&] { return gbs::launch_tree_elim(mp, sh, lv, g0 + q, len, st); }));
+                HIP_TRY(timed(tree_flops(S.n, tree_child_products(S.n - lv - 1)) * (double)len, 0.0, elim, [&] { return gbs::launch_tree_elim(mp, sh, lv, g0 + q, len, st); }));
                 const gbs_status e = run(lv + 1, 2 * (g0 + q), 2 * len);
                 if (e != GBS_OK) return e;
             }
@@ -652,7 +665,7 @@ gbs_status run_sum_tree_dd(DevCtx* c, const double2* A, int N, hipStream_t st, d
     std::function<gbs_status(int, uint64_t, uint64_t)> run = [&](int lv, uint64_t g0, uint64_t count) -> gbs_status {
         if (lv == n) {
             HIP_TRY(timed_launch(
-                kProfCharpoly, gbs_yardstick_flops(2 * n) * (double)count / (double)(1ull << n), (double)count, st,
+                kProfCharpoly, tree_flops(n, (double)count), (double)count, st,
                 [&] { return gbs::launch_tree_dd_leaf(mp, g0, count, terms, st); }, "tree_dd_leaf_kernel"));
             HIP_TRY(timed_launch(kProfSeries, 0.0, (double)count, st, [&] {
                 return gbs::launch_lds_block_reduce(1, terms, count, kPer, c->partials + 5 * poff, nullptr, st);
@@ -665,7 +678,8 @@ gbs_status run_sum_tree_dd(DevCtx* c, const double2* A, int N, hipStream_t st, d
             const uint64_t len = std::min(S.piece[lv], count - q);
             mp.win[lv + 1] = g0 + q;
             HIP_TRY(timed_launch(
-                kProfCharpoly, 0.0, 0.0, st, [&] { return gbs::launch_tree_dd_elim(mp, lv, g0 + q, len, st); },
+                kProfCharpoly, tree_flops(n, tree_child_products(n - lv - 1)) * (double)len, 0.0, st,
+                [&] { return gbs::launch_tree_dd_elim(mp, lv, g0 + q, len, st); },
                 "tree_dd_elim_kernel"));
             ++nl;
             const gbs_status e = run(lv + 1, 2 * (g0 + q), 2 * len);

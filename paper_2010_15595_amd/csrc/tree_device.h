@@ -372,6 +372,56 @@ __device__ __forceinline__ double2 leaf_term(S ps, S qs) {
     return make_double2(acc[NN].x * (1.0 / NN), acc[NN].y * (1.0 / NN));
 }
 
+// Level-0 entries of one root: with a = A with zero diagonal, symmetrised, d its
+// diagonal and G the rotation whose rows for pair (i, i + n) are
+// (e_i + e_(i+n)) / sqrt 2 and -i (e_i - e_(i+n)) / sqrt 2, so that G^T G swaps the
+// pair: entry (j, k) = (G a G^T)_jk, entry (j, border) = (G d)_j, constant
+// series.  An odd N gets one more vertex with loop weight 1 and no edges.
+__device__ __forceinline__ double2 root_at(const double2* A, int N, int r, int c) {
+    if (r == c || r >= N || c >= N) return make_double2(0.0, 0.0);
+    const double2 x = A[r * N + c], y = A[c * N + r];
+    return make_double2(0.5 * (x.x + y.x), 0.5 * (x.y + y.y));
+}
+__device__ __forceinline__ double2 root_loop(const double2* A, int N, int r) {
+    return r < N ? A[r * N + r] : make_double2(1.0, 0.0);
+}
+
+// Coefficient 0 of entry e, the only one that is not zero.
+__device__ __forceinline__ double2 root_entry(const double2* A, int N, int n, int e) {
+    double2 v = make_double2(0.0, 0.0);
+    if (e > 0) {
+        const int x = e - 1;
+        int j = (int)((__builtin_sqrtf(8.0f * (float)x + 1.0f) - 1.0f) * 0.5f);
+        if (tree_tri(j + 1, 0) <= x) ++j;
+        if (tree_tri(j, 0) > x) --j;
+        const int k = x - tree_tri(j, 0);
+        const int pj = (j - 1) >> 1, pk = (k - 1) >> 1;   // pairs
+        const bool vj = ((j - 1) & 1) != 0, vk = ((k - 1) & 1) != 0;  // second vertex of the pair
+        if (k == 0 && j > 0) {
+            const double2 a = root_loop(A, N, pj), b = root_loop(A, N, pj + n);
+            const double h = 0.70710678118654752440;
+            v = vj ? make_double2(h * (a.y - b.y), -h * (a.x - b.x)) : make_double2(h * (a.x + b.x), h * (a.y + b.y));
+        } else if (k > 0) {
+            const double2 a = root_at(A, N, pj, pk), b = root_at(A, N, pj, pk + n);
+            const double2 c = root_at(A, N, pj + n, pk), d = root_at(A, N, pj + n, pk + n);
+            const double sb = vk ? -1.0 : 1.0, sc = vj ? -1.0 : 1.0, sd = sb * sc;
+            const double2 s = make_double2(0.5 * ((a.x + sb * b.x) + (sc * c.x + sd * d.x)),
+                                           0.5 * ((a.y + sb * b.y) + (sc * c.y + sd * d.y)));
+            // times 1, -i or (-i)^2
+            v = (vj && vk) ? make_double2(-s.x, -s.y) : ((vj || vk) ? make_double2(s.y, -s.x) : s);
+        }
+    }
+    return v;
+}
+// Matrix and dimension of root r of a forest.
+__device__ __forceinline__ const double2* root_matrix(const TreeSource& src, uint64_t r, int& N) {
+    N = src.N;
+    if (!src.list) return src.mats;
+    const int i = src.list[r];
+    N = src.dims[i];
+    return src.mats + src.in_off[i];
+}
+
 // Block of node g (level `level` of its item's tree; the item's root is level 0):
 // that of the include child nearest above it, or the root's.
 __device__ __forceinline__ Block node_block(const TreeMap& mp, int level, uint64_t g) {
@@ -447,7 +497,8 @@ __host__ __device__ constexpr int tree_lanes(int T) { return T == 0 ? 4 : tree_e
 // of lanes 9%, which the LDS bandwidth bounds, the leaves 5%.
 template <int NN>
 __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
-    tree_sub_kernel(TreeMap mp, TreeShard sh, int level, uint64_t g0, double* __restrict__ records) {
+    tree_sub_kernel(TreeMap mp, TreeShard sh, int level, uint64_t g0, double* __restrict__ records, TreeSource src,
+                    uint64_t r0) {
     extern __shared__ double2 lds[];
     constexpr int PL = kTreeSlots;
     double2* line = lds + NN * PL;
@@ -464,8 +515,23 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
     }
     double2 sa[NN + 1], sb[NN + 1];
     if (lane < NN) row(kTreeOne).put(lane, make_double2(lane == 0 ? 1.0 : 0.0, 0.0));
-    {
-        // the node's prefix to sa, its last pair's rows to LDS
+    // the node's prefix to sa, its last pair's rows to LDS
+    if constexpr (NN <= kTreeDepth) {
+        // a whole tree: from its matrix (with a kernel before this one that writes the
+        // root's entries to memory N = 10 took 22.9 us, now 20.2)
+        int N;
+        const double2* A = tree::root_matrix(src, r0 + g, N);
+        const int Ec = tree_entries(NN - 1), nr = tree_entries(NN) - Ec;
+        const double2 va = tree::root_entry(A, N, NN, lane < Ec ? lane : 0);
+        const double2 vr = tree::root_entry(A, N, NN, Ec + (lane < nr ? lane : 0));
+#pragma unroll
+        for (int k = 0; k <= NN; ++k) sa[k] = make_double2(k ? 0.0 : va.x, k ? 0.0 : va.y);
+        if (lane < nr) {
+#pragma unroll
+            for (int k = 0; k < NN; ++k) row(lane).put(k, sa[1]);
+            row(lane).put(0, vr);
+        }
+    } else {
         const tree::Block root = tree::node_block(mp, level, g);
         const int Ec = tree_entries(T0 - 1), nr = tree_entries(T0) - Ec;
         tree::Cursor pre(root, lane < Ec ? lane : 0), rows(root, Ec + (lane < nr ? lane : 0));

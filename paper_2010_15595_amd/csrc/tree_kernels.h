@@ -44,8 +44,8 @@ __host__ __device__ constexpr int tree_entries(int T) { return 1 + (2 * T + 1) *
 hipError_t launch_tree_root(const TreeMap& mp, const TreeSource& src, uint64_t r0, uint64_t count, hipStream_t st);
 hipError_t launch_tree_elim(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count,
                             hipStream_t st);
-hipError_t launch_tree_sub(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count, double* records,
-                           hipStream_t st);
+hipError_t launch_tree_sub(const TreeMap& mp, const TreeShard& sh, const TreeSource& src, uint64_t r0, int level,
+                           uint64_t g0, uint64_t count, double* records, hipStream_t st);
 // Fixed-order fold of np records into ceil(np / per) records.
 hipError_t launch_records_fold(const double* in, int64_t np, int64_t per, double* out, hipStream_t st);
 // Results of items list[0 .. count-1] (device) from `per` consecutive records

@@ -7,55 +7,14 @@ namespace gbs {
 
 namespace {
 
-// Level-0 entries of one root: with a = A with zero diagonal, symmetrised, d its
-// diagonal and G the rotation whose rows for pair (i, i + n) are
-// (e_i + e_(i+n)) / sqrt 2 and -i (e_i - e_(i+n)) / sqrt 2, so that G^T G swaps the
-// pair: entry (j, k) = (G a G^T)_jk, entry (j, border) = (G d)_j, constant
-// series.  An odd N gets one more vertex with loop weight 1 and no edges.
-__device__ __forceinline__ double2 at(const double2* A, int N, int r, int c) {
-    if (r == c || r >= N || c >= N) return make_double2(0.0, 0.0);
-    const double2 x = A[r * N + c], y = A[c * N + r];
-    return make_double2(0.5 * (x.x + y.x), 0.5 * (x.y + y.y));
-}
-__device__ __forceinline__ double2 loop_at(const double2* A, int N, int r) {
-    return r < N ? A[r * N + r] : make_double2(1.0, 0.0);
-}
-
 __global__ void __launch_bounds__(64) tree_root_kernel(TreeMap mp, TreeSource src, uint64_t r0, int blocks) {
     const int n = mp.n, E = tree_entries(n);
     const unsigned r = blockIdx.x / blocks;
     const int e = (int)(blockIdx.x % blocks) * 64 + threadIdx.x;
     if (e >= E) return;
-    const double2* A = src.mats;
-    int N = src.N;
-    if (src.list) {
-        const int i = src.list[r0 + r];
-        A += src.in_off[i];
-        N = src.dims[i];
-    }
-    double2 v = make_double2(0.0, 0.0);
-    if (e > 0) {
-        const int x = e - 1;
-        int j = (int)((__builtin_sqrtf(8.0f * (float)x + 1.0f) - 1.0f) * 0.5f);
-        if (tree_tri(j + 1, 0) <= x) ++j;
-        if (tree_tri(j, 0) > x) --j;
-        const int k = x - tree_tri(j, 0);
-        const int pj = (j - 1) >> 1, pk = (k - 1) >> 1;   // pairs
-        const bool vj = ((j - 1) & 1) != 0, vk = ((k - 1) & 1) != 0;  // second vertex of the pair
-        if (k == 0 && j > 0) {
-            const double2 a = loop_at(A, N, pj), b = loop_at(A, N, pj + n);
-            const double h = 0.70710678118654752440;
-            v = vj ? make_double2(h * (a.y - b.y), -h * (a.x - b.x)) : make_double2(h * (a.x + b.x), h * (a.y + b.y));
-        } else if (k > 0) {
-            const double2 a = at(A, N, pj, pk), b = at(A, N, pj, pk + n);
-            const double2 c = at(A, N, pj + n, pk), d = at(A, N, pj + n, pk + n);
-            const double sb = vk ? -1.0 : 1.0, sc = vj ? -1.0 : 1.0, sd = sb * sc;
-            const double2 s = make_double2(0.5 * ((a.x + sb * b.x) + (sc * c.x + sd * d.x)),
-                                           0.5 * ((a.y + sb * b.y) + (sc * c.y + sd * d.y)));
-            // times 1, -i or (-i)^2
-            v = (vj && vk) ? make_double2(-s.x, -s.y) : ((vj || vk) ? make_double2(s.y, -s.x) : s);
-        }
-    }
+    int N;
+    const double2* A = tree::root_matrix(src, r0 + r, N);
+    const double2 v = tree::root_entry(A, N, n, e);
     double2* p = mp.arena + mp.off[0] + (uint64_t)r * (uint64_t)(E * (n + 1)) + e;
     p[0] = v;
     for (int k = 1; k <= n; ++k) p[k * E] = make_double2(0.0, 0.0);
@@ -173,6 +132,8 @@ struct TreeSubArgs {
     int level;
     uint64_t g0, count;
     double* records;
+    const TreeSource* src;
+    uint64_t r0;
 };
 
 template <class K>
@@ -213,7 +174,7 @@ hipError_t tree_elim_inst(const TreeElimArgs& a, hipStream_t st) {
 template <int NN>
 hipError_t tree_sub_inst(const TreeSubArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(tree_sub_kernel<NN>, dim3((unsigned)a.count), dim3(64), tree_sub_lds(NN), st, *a.mp, *a.sh, a.level, a.g0,
-                       a.records);
+                       a.records, *a.src, a.r0);
     return hipGetLastError();
 }
 
@@ -287,12 +248,12 @@ hipError_t launch_tree_elim(const TreeMap& mp, const TreeShard& sh, int level, u
     return tree_elim_n<1>(n, a, st);
 }
 
-hipError_t launch_tree_sub(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count, double* records,
-                           hipStream_t st) {
+hipError_t launch_tree_sub(const TreeMap& mp, const TreeShard& sh, const TreeSource& src, uint64_t r0, int level,
+                           uint64_t g0, uint64_t count, double* records, hipStream_t st) {
     const int n = mp.n;
     if (count == 0) return hipSuccess;
     if (n < 1 || n > kTreeMaxPairs || n - level > kTreeDepth || count > (uint64_t)INT32_MAX) return hipErrorInvalidValue;
-    const TreeSubArgs a{&mp, &sh, level, g0, count, records};
+    const TreeSubArgs a{&mp, &sh, level, g0, count, records, &src, r0};
     return tree_sub_n<1>(n, a, st);
 }
 
