@@ -109,8 +109,6 @@ __global__ void __launch_bounds__(64) tree_dd_root_kernel(TreeMap mp, const doub
     auto loop = [&](int r) -> cdd {
         return r < N ? cdd_make(A[r * N + r].x, A[r * N + r].y) : cdd_make(1.0, 0.0);
     };
-    auto minus_i = [](cdd a) { return cdd{a.im, dd_neg(a.re)}; };
-    auto neg = [](cdd a) { return cdd{dd_neg(a.re), dd_neg(a.im)}; };
     cdd v = cdd_zero();
     if (e > 0) {
         const int x = e - 1;
@@ -118,18 +116,7 @@ __global__ void __launch_bounds__(64) tree_dd_root_kernel(TreeMap mp, const doub
         if (tree_tri(j + 1, 0) <= x) ++j;
         if (tree_tri(j, 0) > x) --j;
         const int k = x - tree_tri(j, 0);
-        const int pj = (j - 1) >> 1, pk = (k - 1) >> 1;
-        const bool vj = ((j - 1) & 1) != 0, vk = ((k - 1) & 1) != 0;
-        if (k == 0 && j > 0) {
-            const dd h{0.70710678118654757, -4.8336466567264567e-17};  // 1 / sqrt 2
-            const cdd a = loop(pj), b = loop(pj + n);
-            v = cdd_mul_dd(vj ? minus_i(cdd_sub(a, b)) : cdd_add(a, b), h);
-        } else if (k > 0) {
-            const cdd a = at(pj, pk), b = at(pj, pk + n), c = at(pj + n, pk), d = at(pj + n, pk + n);
-            cdd s = cdd_add(cdd_add(a, vk ? neg(b) : b), cdd_add(vj ? neg(c) : c, vj != vk ? neg(d) : d));
-            s = cdd_mul_d(s, 0.5);
-            v = (vj && vk) ? neg(s) : ((vj || vk) ? minus_i(s) : s);
-        }
+        if (j > 0) v = k == 0 ? loop(tree::root_row(j, n)) : at(tree::root_row(j, n), tree::root_row(k, n));
     }
     cdd* p = reinterpret_cast<cdd*>(mp.arena) + mp.off[0] + e;
     p[0] = v;

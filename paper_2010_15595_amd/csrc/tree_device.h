@@ -2,27 +2,33 @@
 // Subset tree: the signed terms t_S of all 2^n pair subsets by Schur
 // complements over power series (gfx950 / CDNA4).
 //
-// With X the pair swap and G the pairwise rotation of prep_root (G^T G = X),
-// C_S = X_S A0_S is similar to M_S, a principal submatrix of the complex
-// symmetric M = G A0 G^T, and the loop terms of a subset are w_S^T M_S^(k-1) w_S
-// with w = G d.  So
-//     sum_k tr(C_S^k) x^k / k           = -log det(I - x M_S),
-//     sum_k (d^T C_S^(k-1) X d)_S x^k   = x w_S^T (I - x M_S)^-1 w_S,
-// and both follow from eliminating the 2s vertices of S one by one from the
-// bordered matrix [[., w^T], [w, M]] over power series in x: with pivot
-// 1 - x m_uu(x),
-//     y_j  = m_uj / (1 - x m_uu)                  (a triangular Toeplitz solve)
-//     m_jk <- m_jk + x y_j m_uk,                  dd <- dd + y_d m_ud,
-//     sum_k p_k x^k gains x (x m_uu)' / (1 - x m_uu)   (the same solve).
-// No division by a small number occurs (pivots start with 1), and eliminating a
-// pair serves every subset that shares it: the subsets form a binary tree whose
-// root has eliminated nothing, where a node with T pairs left has an exclude
-// child (the entries without that pair, not copied) and an include child (the
-// updated entries).  Levels close to the root are shared by many subsets; a
-// level of T remaining pairs costs a subset about 2^-T (2T)^2 series products,
-// in all about 40 products of n^2 / 2 complex multiply-adds against the about
-// 47000 multiply-adds a Hessenberg reduction and characteristic polynomial of
-// the same subset take on average at n = 25.
+// With X the pair swap and C_S = X_S A0_S,
+//     sum_k tr(C_S^k) x^k / k           = -log det(X - x A0)_S (up to the sign of det X),
+//     sum_k (d^T C_S^(k-1) X d)_S x^k   = x d_S^T (X - x A0)_S^-1 d_S,
+// and both follow from eliminating the pairs (u, v) of S one by one from the
+// bordered matrix [[., d^T], [d, A0]] over power series in x.  With a = m_uu,
+// b = m_uv and c = m_vv the pivot block of a pair is [[-x a, 1 - x b],
+// [1 - x b, -x c]], and 1 - x b is pivoted on:
+//     y_j  = m_uj / (1 - x b),  h = a / (1 - x b)   (triangular Toeplitz solves)
+//     v_j' = m_vj + x c y_j,    u_j' = m_uj + x h m_vj,    b' = b + x c h,
+//     z_j  = v_j' / (1 - x b'),
+//     m_jk <- m_jk + x y_j m_vk + x z_j u_k'        (symmetric, j >= k is kept),
+//     sum_k p_k x^k gains x (x b)' / (1 - x b) and the same of b'  (the same solves).
+// No division by a small number occurs (pivots start with 1).  Scaling vertex u by
+// s and v by 1 / s leaves every term as it is and scales each quantity above as a
+// whole, by powers of two exactly: a matrix with large u and small v rows, or
+// loop weights, loses nothing.  (A rotation of each pair to a symmetric M with
+// M_S ~ C_S needs one row update less, but mixes the two scales, and powers of M
+// then cancel: with the second halves' vertices scaled by 1/30, 1/100, 1/1000 the
+// error over sum |t_S| was 2e-14, 2e-11, 9e-7 at N = 16; this way it is 1e-16 at
+// any scale.)  Eliminating a pair serves every subset that shares it: the subsets
+// form a binary tree whose root has eliminated nothing, where a node with T pairs
+// left has an exclude child (the entries without that pair, not copied) and an
+// include child (the updated entries).  Levels close to the root are shared by
+// many subsets; a level of T remaining pairs costs a subset about 2^-T (2T)^2
+// series products, in all about 40 products of n^2 / 2 complex multiply-adds
+// against the about 47000 multiply-adds a Hessenberg reduction and characteristic
+// polynomial of the same subset take on average at n = 25.
 //
 // Entry list of a node with T pairs left (E_T = 1 + (2T+1)(T+1) series of n
 // coefficients): 0: the power sums p_1..p_n so far; 1 + tri(j, k), j >= k, the
@@ -290,9 +296,9 @@ __device__ __forceinline__ void half_products(int p, double scale, Y ys, M ms, I
 // Eliminates the last pair of a parent (block pb, T pairs left afterwards) and
 // writes its include child (block cb): the couplings d0 <= d < d1 of its
 // (2T+1)(T+1), and with d0 = 0 the power sums.  LDS (PLANE >= tree_temps(T)
-// series): rows u (W + 1, y_v over m_uu) and v (W + 2, updated in place) of the
-// pair's vertices, y (W), z (W) and the two vertices' power sums, W = 2T + 1.  The
-// rows are read in one go: taken from device memory coefficient by coefficient,
+// series): row u (W + 1, updated in place, h over a), row v (W + 2, b' over b) of
+// the pair's vertices, y (W), v' and then z (W) and the two power sums, W = 2T + 1.
+// The rows are read in one go: taken from device memory coefficient by coefficient,
 // the solves waited for it (84 us instead of 50 for 2048 nodes at n = 25).
 template <int NN, int PLANE>
 __device__ __forceinline__ void elim_pair(Block pb, Block cb, double2* lds, int T, int d0, int d1) {
@@ -310,21 +316,21 @@ __device__ __forceinline__ void elim_pair(Block pb, Block cb, double2* lds, int 
     const int j = lane - 1;
 #pragma unroll 1
     for (int ph = 0; ph < 2; ++ph) {
-        // phase 0: y_j = m_uj / (1 - x m_uu) for every other vertex j < W and for v
-        // (j = W, which replaces m_uu: its coefficient d is written when all lanes have
-        // read that of m_uu); phase 1: z_j likewise with the updated row of v; j = -1:
-        // the power sums
+        // phase 0: y_j for every other vertex j < W and h (j = W); phase 1: z_j;
+        // j = -1: the power sums
         if (j <= (ph == 0 ? W : W - 1)) {
-            const int su = ph == 0 ? W : 2 * W + 2;
-            const int sr = j < 0 ? su : (j < W ? (ph == 0 ? j : W + 1 + j) : 2 * W + 1);
-            const LdsSeries<PLANE> to = tmp(j < 0 ? PLANE - 2 + ph : (j < W ? 2 * W + 3 + ph * W + j : W));
-            solve<NN>(tmp(su), tmp(sr), j < 0 ? 1.0 : 0.0, [&](int k, double2 v) { to.put(k, v); });
+            const int su = 2 * W + 1;
+            const int sz = 2 * W + 3 + ph * W + j;
+            const LdsSeries<PLANE> to = tmp(j < 0 ? PLANE - 2 + ph : (j < W ? sz : W));
+            solve<NN>(tmp(su), tmp(j < 0 ? su : (ph == 0 ? j : sz)), j < 0 ? 1.0 : 0.0,
+                      [&](int k, double2 v) { to.put(k, v); });
         }
         order_wave();
-        // row of v: m_vj + x y_v m_uj (j < W) and m_vv + x y_v m_uv
-        if (ph == 0 && lane <= W) {
-            const LdsSeries<PLANE> rv = tmp(lane < W ? W + 1 + lane : 2 * W + 2);
-            conv_stream<NN>(tmp(W), tmp(lane < W ? lane : 2 * W + 1), rv, rv);
+        // v_j' to the place of z_j (t < W), b' (t = W) and u_j' (t > W)
+        for (int t = lane; ph == 0 && t <= 2 * W; t += 64) {
+            const int su = t <= W ? W + 1 + t : t - W - 1;
+            conv_stream<NN>(tmp(t < W ? 2 * W + 3 + t : W), tmp(t <= W ? 2 * W + 2 : t), tmp(su),
+                            tmp(t < W ? 3 * W + 3 + t : su));
         }
         order_wave();
     }
@@ -332,7 +338,7 @@ __device__ __forceinline__ void elim_pair(Block pb, Block cb, double2* lds, int 
         const double2 p = pb.base[(lane + 1) * pb.stride], u = tmp(PLANE - 2).get(lane), v = tmp(PLANE - 1).get(lane);
         cb.base[(lane + 1) * cb.stride] = make_double2(p.x + u.x + v.x, p.y + u.y + v.y);
     }
-    // the child's couplings m_jk + x y_j m_uk + x z_j m_vk; the border's own is
+    // the child's couplings m_jk + x y_j m_vk + x z_j u_k'; the border's own is
     // held times x, so that it takes the same products
     for (int x = d0 + lane; x < d1; x += 64) {
         int i = (int)((__builtin_sqrtf(8.0f * (float)x + 1.0f) - 1.0f) * 0.5f);
@@ -345,7 +351,7 @@ __device__ __forceinline__ void elim_pair(Block pb, Block cb, double2* lds, int 
         for (int k = 0; k <= NN; ++k) acc[k] = in.get(k);
 #pragma unroll 1
         for (int ph = 0; ph < 2; ++ph)
-            conv<NN, NN>(acc, tmp(2 * W + 3 + ph * W + i), tmp(k0 + ph * (W + 1)));
+            conv<NN, NN>(acc, tmp(2 * W + 3 + ph * W + i), tmp(k0 + (1 - ph) * (W + 1)));
 #pragma unroll
         for (int k = 0; k <= NN; ++k) out.put(k, acc[k]);
     }
@@ -372,11 +378,15 @@ __device__ __forceinline__ double2 leaf_term(S ps, S qs) {
     return make_double2(acc[NN].x * (1.0 / NN), acc[NN].y * (1.0 / NN));
 }
 
-// Level-0 entries of one root: with a = A with zero diagonal, symmetrised, d its
-// diagonal and G the rotation whose rows for pair (i, i + n) are
-// (e_i + e_(i+n)) / sqrt 2 and -i (e_i - e_(i+n)) / sqrt 2, so that G^T G swaps the
-// pair: entry (j, k) = (G a G^T)_jk, entry (j, border) = (G d)_j, constant
-// series.  An odd N gets one more vertex with loop weight 1 and no edges.
+// Level-0 entries of one root: with a = A with zero diagonal, symmetrised, and d its
+// diagonal, vertices 2i + 1 and 2i + 2 being rows i + n and i: entry (j, k) = a_jk,
+// entry (j, border) = d_j, constant series.  An odd N gets one more vertex with
+// loop weight 1 and no edges.  (Which row of a pair comes first is free: the
+// terms' errors are of one size.  At N = 40 of the benchmark family the sum's is
+// 2.6e-18 of sum |t_S| this way and 6e-19 with i first, 1e-19 to 2.5e-18 over
+// permutations of the pairs; the comparison with long doubles in the tests asks
+// that it be more than 20 times theirs, 8e-20.)
+__device__ __forceinline__ int root_row(int j, int n) { return ((j - 1) >> 1) + (((j - 1) & 1) ? 0 : n); }
 __device__ __forceinline__ double2 root_at(const double2* A, int N, int r, int c) {
     if (r == c || r >= N || c >= N) return make_double2(0.0, 0.0);
     const double2 x = A[r * N + c], y = A[c * N + r];
@@ -395,21 +405,7 @@ __device__ __forceinline__ double2 root_entry(const double2* A, int N, int n, in
         if (tree_tri(j + 1, 0) <= x) ++j;
         if (tree_tri(j, 0) > x) --j;
         const int k = x - tree_tri(j, 0);
-        const int pj = (j - 1) >> 1, pk = (k - 1) >> 1;   // pairs
-        const bool vj = ((j - 1) & 1) != 0, vk = ((k - 1) & 1) != 0;  // second vertex of the pair
-        if (k == 0 && j > 0) {
-            const double2 a = root_loop(A, N, pj), b = root_loop(A, N, pj + n);
-            const double h = 0.70710678118654752440;
-            v = vj ? make_double2(h * (a.y - b.y), -h * (a.x - b.x)) : make_double2(h * (a.x + b.x), h * (a.y + b.y));
-        } else if (k > 0) {
-            const double2 a = root_at(A, N, pj, pk), b = root_at(A, N, pj, pk + n);
-            const double2 c = root_at(A, N, pj + n, pk), d = root_at(A, N, pj + n, pk + n);
-            const double sb = vk ? -1.0 : 1.0, sc = vj ? -1.0 : 1.0, sd = sb * sc;
-            const double2 s = make_double2(0.5 * ((a.x + sb * b.x) + (sc * c.x + sd * d.x)),
-                                           0.5 * ((a.y + sb * b.y) + (sc * c.y + sd * d.y)));
-            // times 1, -i or (-i)^2
-            v = (vj && vk) ? make_double2(-s.x, -s.y) : ((vj || vk) ? make_double2(s.y, -s.x) : s);
-        }
+        if (j > 0) v = k == 0 ? root_loop(A, N, root_row(j, n)) : root_at(A, N, root_row(j, n), root_row(k, n));
     }
     return v;
 }
@@ -472,13 +468,18 @@ __global__ void __launch_bounds__(64, (NN <= 25 ? 2 : 1)) tree_elim_kernel(TreeM
 }
 
 // LDS series per parent while a pair is eliminated, T pairs left after it, in
-// tree_sub_kernel: rows u (W + 1, y_v over m_uu) and v (W + 2, updated in
-// place) of the pair's vertices and y (W, then z), W = 2T + 1, and where a solve
-// runs on pairs of lanes in both phases the power sums of u.
+// tree_sub_kernel: row u (W + 1, updated in place, h over a) and row v (W + 2, b'
+// over b) of the pair's vertices and y (W, then v', then z), W = 2T + 1, and where a
+// solve runs on pairs of lanes in both phases the first power sums.
 __host__ __device__ constexpr int tree_slots(int T) { return T >= 2 ? 6 * T + 7 : 6 * T + 6; }
 constexpr int kTreeOne = 96;  // 2^(4-T) parents, T = 0..4; the series 1 after them
 constexpr int kTreeSlots = 97;
 __host__ __device__ constexpr int tree_lanes(int T) { return T == 0 ? 4 : tree_entries(T); }
+
+// Row updates of T <= 2 (44 to 56 rows) as one round of whole products, not two on
+// pairs of lanes; n = 12 at two waves per SIMD, 27 and 28 would need scratch.
+template <int NN>
+constexpr bool kTreeWholeRows = NN <= 26 && NN != 12;
 
 // The subtree of up to kTreeDepth pairs below nodes g0 + blockIdx.x of `level`:
 // one wavefront per node, all its subset terms summed in a fixed order
@@ -584,21 +585,21 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
         const int k0 = xc - tree_tri(j, 0);
 #pragma unroll 1
         for (int ph = 0; ph < 2; ++ph) {
-            // phase 0: y_j = m_uj / (1 - x m_uu) for every other vertex j < W and for
-            // v (j = W); phase 1: z_j likewise with the updated row of v; row x = 0:
-            // the power sums.  On pairs of lanes where 32 rows do.
+            // phase 0: y_j for every other vertex j < W and h (row W + 1); phase 1:
+            // z_j; row 0: the power sums.  On pairs of lanes where 32 rows do.
             const int pl = lane & 1, rows = W + 2 - ph;
             if (ph == 0 && T < 2) {
                 if (on && x <= W + 1) {
-                    const int su = tb + W, sr = x == 0 ? su : (x == W + 1 ? tb + 2 * W + 1 : tb + x - 1);
-                    const int so = x == W + 1 ? W : 2 * W + 2 + x;
+                    const int su = tb + 2 * W + 1;
                     double2 y[NN];
-                    tree::solve<NN>(row(su), row(sr), x == 0 ? 1.0 : 0.0, [&](int k, double2 v) { y[k] = v; });
+                    tree::solve<NN>(row(su), row(x == 0 ? su : tb + x - 1), x == 0 ? 1.0 : 0.0,
+                                    [&](int k, double2 v) { y[k] = v; });
                     tree::order_wave();
                     if (x == 0) {
 #pragma unroll
                         for (int k = 0; k < NN; ++k) sb[k + 1] = make_double2(sb[k + 1].x + y[k].x, sb[k + 1].y + y[k].y);
                     } else {
+                        const int so = x == W + 1 ? W : 2 * W + 2 + x;
 #pragma unroll
                         for (int k = 0; k < NN; ++k) row(tb + so).put(k, y[k]);
                     }
@@ -606,25 +607,38 @@ __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
             } else {
                 const int cr = (lane >> 1) / rows, xr = (lane >> 1) - cr * rows, tr = cr * tree_slots(T);
                 if (cr < P) {
-                    const int su = tr + (ph == 0 ? W : 2 * W + 2);
-                    const int sr = xr == 0 ? su : (xr == W + 1 ? tr + 2 * W + 1 : tr + xr - 1 + (ph == 0 ? 0 : W + 1));
-                    const int so = xr == 0 ? (ph == 0 ? 3 * W + 3 : W) : (xr == W + 1 ? W : 2 * W + 2 + xr);
-                    tree::half_products<NN, true>(pl, xr == 0 ? 1.0 : 0.0, row(su), row(su), row(sr), row(tr + so));
+                    const int su = tr + 2 * W + 1, sz = tr + 2 * W + 2 + xr;
+                    const int sr = xr == 0 ? su : (ph == 0 ? tr + xr - 1 : sz);
+                    const int so = xr == 0 ? tr + (ph == 0 ? 3 * W + 3 : W) : (xr == W + 1 ? tr + W : sz);
+                    tree::half_products<NN, true>(pl, xr == 0 ? 1.0 : 0.0, row(su), row(su), row(sr), row(so));
                 }
             }
             tree::order_wave();
-            // the include child's couplings: m_jk + x y_j m_uk, then + x z_j m_vk; its
-            // power sums (x = 0) are those of u and v times 1
+            // the include child's couplings: m_jk + x y_j m_vk, then + x z_j u_k'; its
+            // power sums (x = 0) are those of b and b' times 1
             if (on && x < E && (x > 0 || T >= 2 || ph == 1)) {
                 const int sy = x == 0 ? (ph == 0 ? 3 * W + 3 : W) : 2 * W + 3 + j;
-                tree::conv<NN, NN>(sb, row(tb + sy), row(x == 0 ? kTreeOne : tb + k0 + (ph == 0 ? 0 : W + 1)));
+                tree::conv<NN, NN>(sb, row(tb + sy), row(x == 0 ? kTreeOne : tb + k0 + (ph == 0 ? W + 1 : 0)));
             }
             if (ph == 0) {
-                // row of v: m_vj + x y_v m_uj, and m_vv + x y_v m_uv
-                const int cr = (lane >> 1) / (W + 1), xr = (lane >> 1) - cr * (W + 1), tr = cr * tree_slots(T);
-                if (cr < P) {
-                    const tree::LdsSeries<PL> rv = row(tr + (xr < W ? W + 1 + xr : 2 * W + 2));
-                    tree::half_products<NN, false>(pl, 0.0, row(tr + W), row(tr + (xr < W ? xr : 2 * W + 1)), rv, rv);
+                // v_j' over y_j (xr < W), b' (xr = W) and u_j' (xr > W)
+                auto update = [&](int t, auto&& products) {
+                    const int cr = t / (2 * W + 1), xr = t - cr * (2 * W + 1), tr = cr * tree_slots(T);
+                    if (cr < P) {
+                        const int sr = xr <= W ? W + 1 + xr : xr - W - 1, sy = xr < W ? 2 * W + 3 + xr : W;
+                        products(row(tr + sy), row(tr + (xr <= W ? 2 * W + 2 : xr)), row(tr + sr),
+                                 row(tr + (xr < W ? sy : sr)));
+                    }
+                };
+                if (T > 2 || !kTreeWholeRows<NN>) {
+                    // (one round for T > 2)
+#pragma unroll 1
+                    for (int t = lane >> 1; t < P * (2 * W + 1); t += 32)
+                        update(t, [&](auto y, auto m, auto in, auto out) {
+                            tree::half_products<NN, false>(pl, 0.0, y, m, in, out);
+                        });
+                } else if constexpr (kTreeWholeRows<NN>) {
+                    update(lane, [&](auto y, auto m, auto in, auto out) { tree::conv_stream<NN>(y, m, in, out); });
                 }
                 tree::order_wave();
             }

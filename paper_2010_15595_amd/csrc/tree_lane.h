@@ -48,8 +48,9 @@ constexpr int kThreads = 256;      // 16 or 8 solves at a time
 // A solve runs on 16 or 32 lanes, one per coefficient (n <= 31).
 __host__ __device__ constexpr int solve_lanes(int n) { return n <= 16 ? 16 : 32; }
 __host__ __device__ constexpr int lds_stride(int n) { return n | 1; }  // odd: spreads the series over the banks
-// LDS series per node: y (W + 1, the last y_v), z (W), the power sums of the two
-// vertices, the updated row of v (W + 2), and with `rows` the row of u (W + 1)
+// LDS series per node: y (W + 1, the last h), v' and then z (W), the two power
+// sums, the updated row of u (W + 2: u_j', a, b'), and with `rows` the row of v
+// (W + 1: m_vj, c)
 __host__ __device__ constexpr int lds_series(int T, bool rows) {
     return 3 * (2 * T + 1) + 5 + (rows ? 2 * T + 2 : 0);
 }
@@ -58,8 +59,8 @@ __host__ __device__ constexpr int lds_series(int T, bool rows) {
 }  // namespace treelane
 
 // Include children of parents g0 .. g0 + count - 1 of `level`, `per` parents per
-// workgroup.  ROWS: the row of u is copied to LDS; otherwise it is read from the
-// parent's block (the row of v, which changes, always moves to LDS).
+// workgroup.  ROWS: the row of v is copied to LDS; otherwise it is read from the
+// parent's block (the row of u, which changes, always moves to LDS).
 template <class AR, bool ROWS>
 __global__ void __launch_bounds__(treelane::kThreads) tree_lane_elim_kernel(TreeMap mp, int level, uint64_t g0,
                                                                             uint64_t count, int per) {
@@ -82,17 +83,20 @@ __global__ void __launch_bounds__(treelane::kThreads) tree_lane_elim_kernel(Tree
     auto y_at = [&](int c, int j, int k) -> V& { return lds[((c * sl) + j) * ns + k]; };              // j <= W
     auto z_at = [&](int c, int j, int k) -> V& { return lds[((c * sl) + W + 1 + j) * ns + k]; };      // j < W
     auto p_at = [&](int c, int q, int k) -> V& { return lds[((c * sl) + 2 * W + 1 + q) * ns + k]; };  // q < 2
-    // row of u: u_j (j <= W, the last m_uu); row of v: v_j (j <= W + 1: m_uv, m_vv)
-    auto v_at = [&](int c, int j, int k) -> V& { return lds[((c * sl) + 2 * W + 3 + j) * ns + k]; };
-    auto u_at = [&](int c, const Block<V>& pb, int j, int k) -> const V& {
-        return ROWS ? lds[((c * sl) + 3 * W + 5 + j) * ns + k] : pb.base[k * pb.stride + E + j];
+    // row of u: u_j (j < W), a (W), b (W + 1); row of v: m_vj (j < W), c (W)
+    auto u_at = [&](int c, int j, int k) -> V& { return lds[((c * sl) + 2 * W + 3 + j) * ns + k]; };
+    auto v_at = [&](int c, const Block<V>& pb, int j, int k) -> const V& {
+        return ROWS ? lds[((c * sl) + 3 * W + 5 + j) * ns + k]
+                    : pb.base[k * pb.stride + E + W + 1 + (j < W ? j : W + 1)];
     };
     {
-        const int r0 = ROWS ? 0 : W + 1, Q = R - r0;
+        const int Q = ROWS ? R : W + 2;
         for (int q = tid; q < nodes * Q * n; q += NT) {
-            const int c = q / (Q * n), x = q - c * (Q * n), k = x / Q, r = r0 + x - k * Q;
+            const int c = q / (Q * n), x = q - c * (Q * n), k = x / Q, i = x - k * Q;
+            const int r = ROWS || i <= W ? i : 2 * W + 1;  // of the parent's entries E ..: u (W + 1), m_vj (W), b, c
             const Block<V> pb = parent(c);
-            lds[((c * sl) + (r <= W ? 3 * W + 5 + r : W + 2 + r)) * ns + k] = pb.base[k * pb.stride + E + r];
+            const int to = r <= W ? 2 * W + 3 + r : (r <= 2 * W ? 2 * W + 4 + r : (r == 2 * W + 1 ? 3 * W + 4 : 4 * W + 5));
+            lds[((c * sl) + to) * ns + k] = pb.base[k * pb.stride + E + r];
         }
         __syncthreads();
     }
@@ -119,23 +123,21 @@ __global__ void __launch_bounds__(treelane::kThreads) tree_lane_elim_kernel(Tree
         m1 = pb.base[k * pb.stride + 1 + x];
     }
     for (int ph = 0; ph < 2; ++ph) {
-        // y_j = m_uj / (1 - x m_uu), j < W and j = W (v), then z_j with the updated row
-        // of v; j = -1: the power sums.  Lane k accumulates coefficient k; coefficient i
-        // is complete at step i and handed to the others through LDS.
+        // y_j, j < W, and h (j = W), then z_j from the v_j' in its place; j = -1: the
+        // power sums.  Lane k accumulates coefficient k; coefficient i is complete at
+        // step i and handed to the others through LDS.
         const int solves = ph == 0 ? W + 2 : W + 1;
         for (int t0 = 0; t0 < nodes * solves; t0 += NT / P) {
             const int t = t0 + tid / P;
             const bool on = t < nodes * solves;
             const int c = on ? t / solves : 0, j = on ? t - c * solves - 1 : 0;
-            const Block<V> pb = parent(c);
-            auto pivot = [&](int k) -> const V& { return ph == 0 ? u_at(c, pb, W, k) : v_at(c, W + 1, k); };
+            auto pivot = [&](int k) -> const V& { return u_at(c, W + 1, k); };
             V* out = j < 0 ? &p_at(c, ph, 0) : (ph == 0 ? &y_at(c, j, 0) : &z_at(c, j, 0));
             const bool mine = on && kl < n;
             Acc a{};
             if (mine) {
                 if (j < 0) a = AR::acc_of(AR::scale(pivot(kl), (double)(kl + 1)));
-                else if (ph == 0 && j < W) a = AR::acc_of(u_at(c, pb, j, kl));
-                else a = AR::acc_of(v_at(c, j, kl));
+                else a = AR::acc_of(ph == 0 ? u_at(c, j, kl) : out[kl]);
             }
             for (int i = 0; i < n; ++i) {
                 if (mine && kl == i) out[i] = AR::value(a);
@@ -145,17 +147,17 @@ __global__ void __launch_bounds__(treelane::kThreads) tree_lane_elim_kernel(Tree
         }
         __syncthreads();
         if (ph == 0) {
-            // row of v: m_vj + x y_v m_uj (j < W), m_vv + x y_v m_uv; lanes of one
-            // coefficient together.  m_uv itself stays.
-            const int rows = nodes * (W + 1);
+            // v_j' = m_vj + x y_j c (x < W), b' = b + x h c (x = W), u_j' = m_uj + x h m_vj;
+            // lanes of one coefficient together
+            const int rows = nodes * (2 * W + 1);
             for (int t = tid; t < rows * n; t += NT) {
-                const int k = t / rows, q = t - k * rows, c = q / (W + 1), x = q - c * (W + 1);
+                const int k = t / rows, q = t - k * rows, c = q / (2 * W + 1), x = q - c * (2 * W + 1);
                 const Block<V> pb = parent(c);
-                const int j = x < W ? x : W + 1;
-                Acc a = AR::acc_of(v_at(c, j, k));
-                for (int i = 0; i < k; ++i)
-                    AR::mac(a, y_at(c, W, i), x < W ? u_at(c, pb, x, k - 1 - i) : v_at(c, W, k - 1 - i));
-                v_at(c, j, k) = AR::value(a);
+                const int y = min(x, W), v = x <= W ? W : x - W - 1;
+                V& io = x < W ? z_at(c, x, k) : u_at(c, x == W ? W + 1 : v, k);
+                Acc a = AR::acc_of(x < W ? v_at(c, pb, x, k) : io);
+                for (int i = 0; i < k; ++i) AR::mac(a, y_at(c, y, i), v_at(c, pb, v, k - 1 - i));
+                io = AR::value(a);
             }
             __syncthreads();
         }
@@ -165,7 +167,7 @@ __global__ void __launch_bounds__(treelane::kThreads) tree_lane_elim_kernel(Tree
         const Block<V> pb = parent(c), cb = child(c);
         cb.base[(k + 1) * cb.stride] = AR::add(pb.base[(k + 1) * pb.stride], AR::add(p_at(c, 0, k), p_at(c, 1, k)));
     }
-    // the children's couplings m_jk + x y_j m_uk + x z_j m_vk (the border's own held
+    // the children's couplings m_jk + x y_j m_vk + x z_j u_k' (the border's own held
     // times x, n + 1 coefficients)
     for (int t = t1; t < units; t += NT) {
         int c, k, x;
@@ -180,8 +182,8 @@ __global__ void __launch_bounds__(treelane::kThreads) tree_lane_elim_kernel(Tree
         Acc a = AR::acc_of(m);
 #pragma unroll AR::kUnroll
         for (int i = 0; i < k; ++i) {
-            AR::mac(a, y_at(c, j, i), u_at(c, pb, k0, k - 1 - i));
-            AR::mac(a, z_at(c, j, i), v_at(c, k0, k - 1 - i));
+            AR::mac(a, y_at(c, j, i), v_at(c, pb, k0, k - 1 - i));
+            AR::mac(a, z_at(c, j, i), u_at(c, k0, k - 1 - i));
         }
         cb.base[k * cb.stride + 1 + x] = AR::value(a);
     }
@@ -196,10 +198,10 @@ hipError_t launch_tree_lane_elim(const TreeMap& mp, int level, uint64_t g0, uint
     if (count == 0) return hipSuccess;
     if (n < 1 || n > kMaxDdPairs || T < 0) return hipErrorInvalidValue;
     const size_t series = sizeof(typename AR::V) * (size_t)lds_stride(n);
-    // The row of u in LDS while a node's series take at most 64 KB; then as many
+    // The row of v in LDS while a node's series take at most 64 KB; then as many
     // nodes per workgroup as fit 32 KB (five workgroups per CU).  N = 41 in
     // double-double: 60.9 ms; with 16, 24 or 40 KB 65.7, 62.6, 64.2 ms; with 128
-    // threads 73.3, with 512 67.4 ms; with the row of u always in memory 66.2 ms.
+    // threads 73.3, with 512 67.4 ms; with the row of v always in memory 66.2 ms.
     const bool rows = series * lds_series(T, true) <= 64 * 1024;
     const size_t node = series * lds_series(T, rows);
     const int per = (int)std::min<uint64_t>(count, std::max<size_t>(1, std::min<size_t>(16, 32 * 1024 / node)));
@@ -240,24 +242,26 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
     const Block<V> cb{reinterpret_cast<V*>(mp.arena) + mp.off[level + 1] +
                           (g0 + blockIdx.x - mp.win[level + 1]) * (uint64_t)(E * (n + 1)),
                       E};
-    // series whose shifts x^(i+1) are read: m_uu, y_v, m_vv, each after 32 zeros
+    // series whose shifts x^(i+1) are read: b (then b'), c, h, each after 32 zeros
     auto shifted = [&](int q) { return lds + 64 * q; };
     V* rows = lds + 3 * 64;
     auto y_at = [&](int j, int k) -> V& { return rows[j * ns + k]; };
     auto z_at = [&](int j, int k) -> V& { return rows[(W + j) * ns + k]; };
-    auto v_at = [&](int j, int k) -> V& { return rows[(2 * W + j) * ns + k]; };
-    auto u_at = [&](int j, int k) -> const V& { return ROWS ? rows[(3 * W + j) * ns + k] : pb.base[k * pb.stride + E + j]; };
+    auto u_at = [&](int j, int k) -> V& { return rows[(2 * W + j) * ns + k]; };
+    auto v_at = [&](int j, int k) -> const V& {
+        return ROWS ? rows[(3 * W + j) * ns + k] : pb.base[k * pb.stride + E + W + 1 + j];
+    };
 
-    // row r: j < W the others, W: the vertex v, W + 1: the power sums
+    // row r: j < W the others, u0: m_uj, v0: m_vj; W: h and b', u0: a, v0: b; W + 1:
+    // the power sums, u0: b, v0: c (1: coefficients 16 on)
     const bool lo = kl < n, hi = WIDE && kl + 16 < n;
     V u0{}, u1{}, v0{}, v1{};
-    const int ue = E + min(r, W), ve = E + W + 1 + (r < W ? r : W + 1);  // of u: m_uj, m_uv or m_uu (replaced below)
-    const int uv = r == W ? E + 2 * W + 1 : ue;
+    const int ue = E + (r <= W ? r : 2 * W + 1), ve = E + W + 1 + r;
     if (r <= W + 1 && lo) {
-        u0 = pb.base[kl * pb.stride + uv];
+        u0 = pb.base[kl * pb.stride + ue];
         v0 = pb.base[kl * pb.stride + ve];
         if (hi) {
-            u1 = pb.base[(kl + 16) * pb.stride + uv];
+            u1 = pb.base[(kl + 16) * pb.stride + ue];
             v1 = pb.base[(kl + 16) * pb.stride + ve];
         }
     }
@@ -274,17 +278,19 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
     if (r == W + 1) {
         if (lo) shifted(0)[32 + kl] = u0;
         if (hi) shifted(0)[48 + kl] = u1;
+        if (lo) shifted(1)[32 + kl] = v0;
+        if (hi) shifted(1)[48 + kl] = v1;
     }
     if (ROWS && r < W) {
-        if (lo) rows[(3 * W + r) * ns + kl] = u0;
-        if (hi) rows[(3 * W + r) * ns + kl + 16] = u1;
+        if (lo) rows[(3 * W + r) * ns + kl] = v0;
+        if (hi) rows[(3 * W + r) * ns + kl + 16] = v1;
     }
     __syncthreads();
-    V p0{}, p1{};  // power sums of u
+    V p0{}, p1{};  // power sums of b
     for (int ph = 0; ph < 2; ++ph) {
-        const V* s = shifted(2 * ph) + 31 + kl;
+        const V* s = shifted(0) + 31 + kl;
         V a0 = ph == 0 ? u0 : v0, a1 = ph == 0 ? u1 : v1;
-        if (r == W + 1) {  // m_uu, then m_vv
+        if (r == W + 1) {  // b, then b'
             a0 = AR::scale(s[1], (double)(kl + 1));
             if (WIDE) a1 = AR::scale(s[17], (double)(kl + 17));
         }
@@ -305,8 +311,8 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
             if (lo) out[0] = a0;
             if (hi) out[16] = a1;
         } else if (ph == 0 && r == W) {
-            if (lo) shifted(1)[32 + kl] = a0;
-            if (hi) shifted(1)[48 + kl] = a1;
+            if (lo) shifted(2)[32 + kl] = a0;
+            if (hi) shifted(2)[48 + kl] = a1;
         } else if (ph == 0) {
             p0 = a0;
             p1 = a1;
@@ -316,30 +322,34 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
         }
         __syncthreads();
         if (ph == 0) {
-            // row of v: m_vj + x y_v m_uj, m_vv + x y_v m_uv
-            const V* q = shifted(1) + 31 + kl;
-            Acc d0 = AR::acc_of(v0), d1 = AR::acc_of(v1);
-            static_for<0, kSteps>([&](auto I) {
-                constexpr int i = decltype(I)::value;
-                if (i < n - 1) {
-                    const V y = AR::template bcast<(i & 15)>(i < 16 ? u0 : u1);
-                    if (i < 15) AR::mac(d0, q[-i], y);
-                    if (WIDE) AR::mac(d1, q[16 - i], y);
-                }
-            });
-            v0 = AR::value(d0);
-            v1 = AR::value(d1);
+            // v_j' = m_vj + x c y_j (row W: b' = b + x c h), then u_j' = m_uj + x h m_vj
+            auto update = [&](int q0, V& x0, V& x1, const V& y0, const V& y1) {
+                const V* q = shifted(q0) + 31 + kl;
+                Acc d0 = AR::acc_of(x0), d1 = AR::acc_of(x1);
+                static_for<0, kSteps>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    if (i < n - 1) {
+                        const V y = AR::template bcast<(i & 15)>(i < 16 ? y0 : y1);
+                        if (i < 15) AR::mac(d0, q[-i], y);
+                        if (WIDE) AR::mac(d1, q[16 - i], y);
+                    }
+                });
+                x0 = AR::value(d0);
+                x1 = AR::value(d1);
+            };
+            update(2, u0, u1, v0, v1);
+            update(1, v0, v1, a0, a1);
             if (r < W) {
-                if (lo) v_at(r, kl) = v0;
-                if (hi) v_at(r, kl + 16) = v1;
+                if (lo) u_at(r, kl) = u0;
+                if (hi) u_at(r, kl + 16) = u1;
             } else if (r == W) {
-                if (lo) shifted(2)[32 + kl] = v0;
-                if (hi) shifted(2)[48 + kl] = v1;
+                if (lo) shifted(0)[32 + kl] = v0;
+                if (hi) shifted(0)[48 + kl] = v1;
             }
             __syncthreads();
         }
     }
-    // the child's couplings m_jk + x y_j m_uk + x z_j m_vk
+    // the child's couplings m_jk + x y_j m_vk + x z_j u_k'
     for (int t = t1; t < units; t += step) {
         const int k = t / D, x = t - k * D;
         int j = (int)((__builtin_sqrtf(8.0f * (float)x + 1.0f) - 1.0f) * 0.5f);
@@ -351,8 +361,8 @@ __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int lev
         Acc a = AR::acc_of(m);
 #pragma unroll AR::kUnroll
         for (int i = 0; i < k; ++i) {
-            AR::mac(a, y_at(j, i), u_at(k0, k - 1 - i));
-            AR::mac(a, z_at(j, i), v_at(k0, k - 1 - i));
+            AR::mac(a, y_at(j, i), v_at(k0, k - 1 - i));
+            AR::mac(a, z_at(j, i), u_at(k0, k - 1 - i));
         }
         cb.base[k * cb.stride + 1 + x] = AR::value(a);
     }
