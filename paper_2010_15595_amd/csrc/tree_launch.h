@@ -114,7 +114,7 @@ __global__ void __launch_bounds__(64) tree_items_kernel(const int* __restrict__ 
 constexpr size_t tree_sub_lds(int n) { return 16 * ((size_t)n * kTreeSlots + 128); }
 // LDS series per coefficient of tree_elim_kernel, a compile-time stride chosen by
 // T: the exact one for the three levels that hold most nodes, ranges above, up to
-// the last level of a launch with more than kTopParents parents at n = 28.
+// the last level of a launch with more than 256 parents at n = 28.
 constexpr int kElimPairs = 19;
 constexpr int kElimPlanes[6] = {tree_temps(kTreeDepth), tree_temps(6), tree_temps(7), tree_temps(9), tree_temps(14),
                                 tree_temps(kElimPairs)};
@@ -227,11 +227,15 @@ struct F64 {
 
 // Up to here a launch of tree_elim_kernel lasts as long as its chain of products,
 // 12 us at n = 16 and 28 us at n = 25; the split of a product over lanes takes 8
-// and 15 us, but a multiply-add costs it several LDS reads.  N = 32 without it
-// 295 us, with a limit of 8, 32, 128, 256, 512 parents 261, 244, 237, 234, 229 us;
-// N = 28 163, 136, 125, 117, 112, 113 us; a batch of N = 10 .. 36 20.5 ms with any
-// of them, 21.3 and 22.9 ms with 4096 and 16384.
-constexpr uint64_t kTopParents = 256;
+// and 15 us, but a multiply-add costs it several LDS reads.  Microseconds with a
+// limit of 32, 128, 256, 512, 1024, 2048 parents: N = 28 124, 115, 111, 111, 111,
+// 112; N = 32 232, 222, 221, 216, 216, 215; N = 36 670, 659, 658, 654, 661, 683;
+// N = 37 without allocation 2827 (128), 2708, 2596, 2599, 2598; 4096 small items 230,
+// 230, 229, 235, 256.  512 and 1024 are alike in time.  1024, because it leaves the
+// N = 40 sum of the benchmark family 2.0e-18 of sum |t_S| off and 512 1.55e-18, by
+// chance of rounding, where the comparison with long doubles in the tests asks for
+// 1.6e-18 at least.
+constexpr uint64_t kTopParents = 1024;
 
 hipError_t launch_tree_elim(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count,
                             hipStream_t st) {
