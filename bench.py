@@ -539,7 +539,8 @@ def fig3_sweep(args, gbs):
         A = workloads.random_uniform_symmetric(N, seed=N)
         A_dev = torch.from_numpy(A).to(dev)
         n = N // 2
-        if not args.no_autotune:
+        # (FP64 sums up to MAX_BATCH_DIM run on the subset tree, which has no lane grid to choose)
+        if not args.no_autotune and N > gbs.MAX_BATCH_DIM:
             gbs.autotune(n)
         gbs.lhaf_device(A_dev, out, ab, stream)
         torch.cuda.synchronize()
@@ -579,7 +580,7 @@ def fig3_sweep(args, gbs):
             _, d = gbs.lhaf(A, prec=gbs.GBS_DD, with_diag=True)
             row["dd_seconds"] = d["kernel_ms"] / 1000.0
             row["dd_speedup_vs_paper"] = paper[N] / row["dd_seconds"] if N in paper else None
-        if not args.no_autotune:
+        if not args.no_autotune and N > gbs.MAX_BATCH_DIM:
             gbs.set_layout(n, 0, -1)
         rows[N] = row
         log(f"N={N}: {row}")
@@ -775,7 +776,8 @@ def main():
     stream = torch.cuda.current_stream(dev)
 
     tuned = None
-    if not args.no_autotune and args.precision != "dd":
+    # FP64 sums up to MAX_BATCH_DIM run on the subset tree, which has no lane grid to choose
+    if not args.no_autotune and (args.precision == "fp32comp" or (args.precision == "fp64" and N > gbs.MAX_BATCH_DIM)):
         t0 = time.perf_counter()
         rep = gbs.autotune(n)
         tuned = {s: lay for s, (lay, _) in rep.items()}
@@ -835,7 +837,7 @@ def main():
                         f"{N} distinct modes occupied",
             "N": N,
             "subset_terms_per_lhaf": int(terms),
-            "lane_grid_per_subset_size": tuned,
+            **({"lane_grid_per_subset_size": tuned} if tuned else {}),
         },
         "subset_terms_per_s": terms * lhaf_per_s,
         "yardstick_flops_per_lhaf": flops,

@@ -734,7 +734,7 @@ gbs_status gbs_batch_plan_create(const int32_t* dims, int32_t count, gbs_precisi
     for (int i = 0; i < count; ++i) {
         if (dims[i] < 0) return fail(GBS_E_ARG, "negative dimension at item %d", i);
         if (dims[i] > gbs::kMaxTileM)
-            return fail(GBS_E_TOO_LARGE, "dimension %d at item %d exceeds %d (batch plans run the register-tile kernels)",
+            return fail(GBS_E_TOO_LARGE, "dimension %d at item %d exceeds %d",
                         dims[i], i, gbs::kMaxTileM);
         dv[i] = dims[i];
     }
@@ -748,8 +748,8 @@ gbs_status gbs_batch_plan_create(const int32_t* dims, int32_t count, gbs_precisi
         if (n >= 1 && !seen[n]) {
             seen[n] = true;
             // items on the subset tree have no lane grid to choose
-            st = ((flags & GBS_PLAN_AUTOTUNE) && !tree_route(c, n, prec == GBS_FP32_COMP)) ? autotune_impl(c, n, nullptr)
-                                                                                           : maybe_tune(c, n);
+            const bool tree = tree_route(c, n, prec == GBS_FP32_COMP);
+            st = ((flags & GBS_PLAN_AUTOTUNE) && !tree) ? autotune_impl(c, n, nullptr) : maybe_tune(c, n, tree);
             if (st != GBS_OK) return st;
         }
     }

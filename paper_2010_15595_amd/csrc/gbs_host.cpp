@@ -840,7 +840,7 @@ gbs_status lhaf_host_matrix(const gbs_z* A, int32_t N, gbs_z* out, gbs_diag* dia
     gbs_status st = current_ctx(&c);
     if (st != GBS_OK) return st;
     const int Np = N + (N & 1);
-    st = maybe_tune(c, Np / 2);
+    st = maybe_tune(c, Np / 2, prec == GBS_FP64 && lds_method < 0 && tree_route(c, Np / 2, false));
     if (st != GBS_OK) return st;
     HIP_TRY(hipStreamWaitEvent(c->stream, c->done, 0));
     if (N > 0) HIP_TRY(hipMemcpyAsync(c->Ain, A, sizeof(gbs_z) * (size_t)N * N, hipMemcpyHostToDevice, c->stream));
@@ -1300,10 +1300,11 @@ gbs_status gbs_lhaf_device(const gbs_z* A_dev, int32_t N, gbs_precision prec, gb
     if (st != GBS_OK) return st;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const int Np = N + (N & 1);
-    st = maybe_tune(c, Np / 2);
+    st = maybe_tune(c, Np / 2, prec == GBS_FP64 && tree_route(c, Np / 2, false));
     if (st != GBS_OK) return st;
     HIP_TRY(hipStreamWaitEvent(s, c->done, 0));
-    st = run_sum(c, reinterpret_cast<const double2*>(A_dev), N, s, reinterpret_cast<double2*>(out_dev), abs_sum_dev, nullptr, prec);
+    st = run_sum(c, reinterpret_cast<const double2*>(A_dev), N, s, reinterpret_cast<double2*>(out_dev), abs_sum_dev,
+                 nullptr, prec);
     if (st != GBS_OK) return st;
     HIP_TRY(hipEventRecord(c->done, s));
     return GBS_OK;
@@ -1326,7 +1327,8 @@ gbs_status gbs_lhaf_device_shard(const gbs_z* A_dev, int32_t N, gbs_precision pr
     st = maybe_tune(c, Np / 2);
     if (st != GBS_OK) return st;
     HIP_TRY(hipStreamWaitEvent(s, c->done, 0));
-    st = run_sum(c, reinterpret_cast<const double2*>(A_dev), N, s, nullptr, nullptr, nullptr, prec, nullptr, -1, shard, nshards, partial_dev);
+    st = run_sum(c, reinterpret_cast<const double2*>(A_dev), N, s, nullptr, nullptr, nullptr, prec, nullptr, -1, shard,
+                 nshards, partial_dev);
     if (st != GBS_OK) return st;
     HIP_TRY(hipEventRecord(c->done, s));
     return GBS_OK;
@@ -1560,10 +1562,14 @@ gbs_status autotune_impl(DevCtx* c, int n, gbs_tune_report* rep) {
     return GBS_OK;
 }
 
-gbs_status maybe_tune(DevCtx* c, int n) {
+gbs_status maybe_tune(DevCtx* c, int n, bool tree) {
     if (n < 1 || n > gbs::kMaxPairs || c->tuned[n]) return GBS_OK;
+    if (!c->cache_read[n]) {
+        c->cache_read[n] = true;
+        c->tuned[n] = cache_load(c, n);
+    }
+    if (tree || c->tuned[n]) return GBS_OK;
     c->tuned[n] = true;
-    if (cache_load(c, n)) return GBS_OK;
     const char* at = std::getenv("GBS_AUTOTUNE");
     if (at && (std::strcmp(at, "1") == 0 || std::strcmp(at, "force") == 0)) return autotune_impl(c, n, nullptr);
     return GBS_OK;

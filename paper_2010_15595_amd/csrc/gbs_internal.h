@@ -68,6 +68,7 @@ struct DevCtx {
     int layout[gbs::kMaxPairs + 1][gbs::kMaxPairs + 1];
     int layout_multi[gbs::kMaxPairs + 1][gbs::kMaxPairs + 1];
     bool tuned[gbs::kMaxPairs + 1];
+    bool cache_read[gbs::kMaxPairs + 1] = {};
     bool forced[gbs::kMaxPairs + 1][gbs::kMaxPairs + 1] = {};  // lane grid chosen by gbs_set_layout
     char name[64] = {0};
     DevCtx() {
@@ -93,8 +94,9 @@ int layout_for(const DevCtx* c, int n, int s, bool batch = false, bool fp32 = fa
 // Tile offset of C for size-s subsets on `lay` (charpoly_front_offset of m = 2s).
 int layout_front_offset(int lay, int s);
 // Consults the autotune cache / runs the tuner once per n (uses the workspace,
-// so it is called before the caller's matrix is prepared).
-gbs_status maybe_tune(DevCtx* c, int n);
+// so it is called before the caller's matrix is prepared).  tree: the call runs on
+// the subset tree and has no lane grid to choose; the tuner is left to one that has.
+gbs_status maybe_tune(DevCtx* c, int n, bool tree = false);
 gbs_status ensure_buffer(void** p, size_t* cap, size_t need, size_t elem);
 // Every device allocation of the library goes through here.  Test hook for the
 // out-of-memory paths: while the environment variable GBS_TEST_FAIL_ALLOC is

@@ -295,7 +295,7 @@ extern "C" gbs_status gbs_sample_pure(const gbs_z* Q, const gbs_z* alpha, int32_
             }
             const int top = *std::max_element(P_tot.begin(), P_tot.begin() + G) + cutoff;  // largest dimension
             for (int n = 1; n <= (top + 1) / 2; ++n)
-                if ((st = maybe_tune(c, n)) != GBS_OK) return st;
+                if ((st = maybe_tune(c, n, tree_route(c, n, fp32))) != GBS_OK) return st;
             batch_schedule(c, dims, fp32, kTileSubsets, kRoundBytes, false, S);
             n_lhaf += S.count;
             n_terms += S.subset_terms;
