@@ -487,12 +487,12 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
     const gbs::TreeShard& sh = shard ? *shard : none;
     const double flops = tree_flops(S.n, tree_sub_products(S.n - S.levels));
     const double subsets = (double)(1ull << (S.n - S.levels));
-    const std::string elim = "tree_elim_kernel<" + std::to_string(S.n) + ">",
-                      sub = "tree_sub_kernel<" + std::to_string(S.n) + ">";
     int nl = 0;
-    auto timed = [&](double f, double c, const std::string& name, const std::function<hipError_t()>& launch) {
+    // no host allocation unless launches are timed
+    auto timed = [&](double f, double c, const char* name, auto&& launch) {
         ++nl;
-        return (prof && profiling_on()) ? prof_charpoly_launch(f, c, st, launch, name) : launch();
+        if (!prof || !profiling_on()) return launch();
+        return prof_charpoly_launch(f, c, st, launch, name + ("<" + std::to_string(S.n)) + ">");
     };
     uint64_t mid = 0, done = 0;  // folded records held in b.mid, records written
     for (uint64_t r0 = 0; r0 < S.items; r0 += S.roots) {
@@ -503,10 +503,10 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
             ++nl;
         }
         // nodes [g0, g0 + count) of level lv, their entries in place
-        std::function<gbs_status(int, uint64_t, uint64_t)> run = [&](int lv, uint64_t g0, uint64_t count) -> gbs_status {
+        auto run = [&](auto&& self, int lv, uint64_t g0, uint64_t count) -> gbs_status {
             if (lv == S.levels) {
                 double* rec = (S.fold > 1) ? b.nodes : records + 5 * ((r0 << lv) + g0);
-                HIP_TRY(timed(flops * (double)count, subsets * (double)count, sub,
+                HIP_TRY(timed(flops * (double)count, subsets * (double)count, "tree_sub_kernel",
                               [&] { return gbs::launch_tree_sub(mp, sh, src, r0, lv, g0, count, rec, st); }));
                 if (S.fold == 1) return GBS_OK;
                 const uint64_t out = count / S.fold;
@@ -529,13 +529,15 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
             for (uint64_t q = 0; q < count; q += S.piece[lv]) {
                 const uint64_t len = std::min(S.piece[lv], count - q);
                 mp.win[lv + 1] = g0 + q;
-                HIP_TRY(timed(tree_flops(S.n, tree_child_products(S.n - lv - 1)) * (double)len, 0.0, elim, [&] { return gbs::launch_tree_elim(mp, sh, lv, g0 + q, len, st); }));
-                const gbs_status e = run(lv + 1, 2 * (g0 + q), 2 * len);
+                HIP_TRY(timed(tree_flops(S.n, tree_child_products(S.n - lv - 1)) * (double)len, 0.0,
+                              gbs::tree_elim_top(S.n, lv, len) ? "tree_top_elim_kernel" : "tree_elim_kernel",
+                              [&] { return gbs::launch_tree_elim(mp, sh, lv, g0 + q, len, st); }));
+                const gbs_status e = self(self, lv + 1, 2 * (g0 + q), 2 * len);
                 if (e != GBS_OK) return e;
             }
             return GBS_OK;
         };
-        const gbs_status e = run(0, 0, roots);
+        const gbs_status e = run(run, 0, 0, roots);
         if (e != GBS_OK) return e;
     }
     if (launches) *launches += nl;
@@ -680,7 +682,7 @@ gbs_status run_sum_tree_dd(DevCtx* c, const double2* A, int N, hipStream_t st, d
             HIP_TRY(timed_launch(
                 kProfCharpoly, tree_flops(n, tree_child_products(n - lv - 1)) * (double)len, 0.0, st,
                 [&] { return gbs::launch_tree_dd_elim(mp, lv, g0 + q, len, st); },
-                "tree_dd_elim_kernel"));
+                gbs::tree_dd_elim_top(len) ? "tree_top_elim_kernel<dd>" : "tree_lane_elim_kernel<dd>"));
             ++nl;
             const gbs_status e = run(lv + 1, 2 * (g0 + q), 2 * len);
             if (e != GBS_OK) return e;

@@ -133,8 +133,10 @@ hipError_t launch_tree_dd_root(const TreeMap& mp, const double2* A, int N, hipSt
 // 531, 520, 521, 540, 565 us.
 constexpr uint64_t kTopParentsDd = 256;
 
+bool tree_dd_elim_top(uint64_t count) { return count <= kTopParentsDd; }
+
 hipError_t launch_tree_dd_elim(const TreeMap& mp, int level, uint64_t g0, uint64_t count, hipStream_t st) {
-    if (count <= kTopParentsDd) return launch_tree_top_elim<treedd::Arith>(mp, level, g0, count, st);
+    if (tree_dd_elim_top(count)) return launch_tree_top_elim<treedd::Arith>(mp, level, g0, count, st);
     return launch_tree_lane_elim<treedd::Arith>(mp, level, g0, count, st);
 }
 

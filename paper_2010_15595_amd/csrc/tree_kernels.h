@@ -44,6 +44,8 @@ __host__ __device__ constexpr int tree_entries(int T) { return 1 + (2 * T + 1) *
 hipError_t launch_tree_root(const TreeMap& mp, const TreeSource& src, uint64_t r0, uint64_t count, hipStream_t st);
 hipError_t launch_tree_elim(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count,
                             hipStream_t st);
+// Whether that runs tree_top_elim_kernel (few parents) or tree_elim_kernel.
+bool tree_elim_top(int n, int level, uint64_t count);
 hipError_t launch_tree_sub(const TreeMap& mp, const TreeShard& sh, const TreeSource& src, uint64_t r0, int level,
                            uint64_t g0, uint64_t count, double* records, hipStream_t st);
 // Fixed-order fold of np records into ceil(np / per) records.
@@ -57,6 +59,8 @@ hipError_t launch_tree_items(const int* list, int count, const double* records, 
 // leaves (level n)
 hipError_t launch_tree_dd_root(const TreeMap& mp, const double2* A, int N, hipStream_t st);
 hipError_t launch_tree_dd_elim(const TreeMap& mp, int level, uint64_t g0, uint64_t count, hipStream_t st);
+// Whether that runs tree_top_elim_kernel or tree_lane_elim_kernel.
+bool tree_dd_elim_top(uint64_t count);
 // Signed terms (double-double) of subset masks g0 .. g0 + count - 1.
 hipError_t launch_tree_dd_leaf(const TreeMap& mp, uint64_t g0, uint64_t count, void* terms, hipStream_t st);
 

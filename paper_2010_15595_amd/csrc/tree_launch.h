@@ -237,12 +237,14 @@ struct F64 {
 // 1.6e-18 at least.
 constexpr uint64_t kTopParents = 1024;
 
+bool tree_elim_top(int n, int level, uint64_t count) { return count <= kTopParents || n - level - 1 > kElimPairs; }
+
 hipError_t launch_tree_elim(const TreeMap& mp, const TreeShard& sh, int level, uint64_t g0, uint64_t count,
                             hipStream_t st) {
     const int n = mp.n, T = n - level - 1;
     if (count == 0) return hipSuccess;
     if (n < 1 || n > kTreeMaxPairs || T < 0) return hipErrorInvalidValue;
-    if (count <= kTopParents || T > kElimPairs) return launch_tree_top_elim<treelane::F64>(mp, level, g0, count, st);
+    if (tree_elim_top(n, level, count)) return launch_tree_top_elim<treelane::F64>(mp, level, g0, count, st);
     if (count > (uint64_t)INT32_MAX) return hipErrorInvalidValue;
     // couplings of larger nodes over several wavefronts, until about two per SIMD
     // are in flight
