@@ -408,6 +408,10 @@ bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid
     S.n = n;
     S.items = items;
     S.levels = n - depth;
+    if (S.levels == 0) {  // a tree is one subtree, whose wavefront reads the matrix itself
+        S.roots = S.sub = std::min<uint64_t>(items, 1ull << 20);
+        return true;
+    }
     const size_t entry = value * (size_t)(n + 1);
     const uint64_t most = budget / entry;
     // roots in flight: all their levels when they fit

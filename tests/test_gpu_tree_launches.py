@@ -84,3 +84,12 @@ def test_plans_of_large_orders():
             w, d = gbs.lhaf(A, with_diag=True)
             assert abs(v - w) <= 2e-14 * d["abs_sum"]
     plan.close()
+
+
+def test_small_orders_keep_no_entry_store():
+    """Up to five pairs a subtree kernel reads the matrices themselves: a plan holds
+    their copy, three doubles and a record of five per item, and its tables."""
+    plan = gbs.BatchPlan([10] * 4000)
+    bytes_ = plan.info()["workspace_bytes"]
+    plan.close()
+    assert bytes_ <= 4000 * (16 * 100 + 100) + (1 << 20)
