@@ -403,6 +403,8 @@ uint64_t piece_entries(TreeSched& S, uint64_t sub) {
 
 }  // namespace
 
+constexpr size_t kTreeBudget = (size_t)4 << 30;  // entry stores of a single evaluation
+
 bool tree_sched(int n, uint64_t items, size_t budget, TreeSched& S, uint64_t mid_records, int depth, size_t value) {
     S = TreeSched();
     S.n = n;
@@ -486,7 +488,8 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
     gbs::TreeMap mp{};
     mp.arena = static_cast<double2*>(b.arena);
     mp.n = S.n;
-    for (int lv = 0; lv <= S.levels; ++lv) mp.off[lv] = S.off[lv] * (uint64_t)(S.n + 1);
+    static_assert(kTreeBudget / sizeof(double2) <= UINT32_MAX, "offsets of an entry store");
+    for (int lv = 0; lv <= S.levels; ++lv) mp.off[lv] = (uint32_t)(S.off[lv] * (uint64_t)(S.n + 1));
     gbs::TreeShard none{};
     const gbs::TreeShard& sh = shard ? *shard : none;
     const double flops = tree_flops(S.n, tree_sub_products(S.n - S.levels));
@@ -501,7 +504,7 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
     uint64_t mid = 0, done = 0;  // folded records held in b.mid, records written
     for (uint64_t r0 = 0; r0 < S.items; r0 += S.roots) {
         const uint64_t roots = std::min(S.roots, S.items - r0);
-        for (uint64_t& w : mp.win) w = 0;
+        for (uint32_t& w : mp.win) w = 0;
         if (S.levels > 0) {
             HIP_TRY(gbs::launch_tree_root(mp, src, r0, roots, st));
             ++nl;
@@ -532,7 +535,7 @@ gbs_status tree_enqueue(const TreeSched& S, const TreeBufs& b, const gbs::TreeSo
             }
             for (uint64_t q = 0; q < count; q += S.piece[lv]) {
                 const uint64_t len = std::min(S.piece[lv], count - q);
-                mp.win[lv + 1] = g0 + q;
+                mp.win[lv + 1] = (uint32_t)(g0 + q);
                 HIP_TRY(timed(tree_flops(S.n, tree_child_products(S.n - lv - 1)) * (double)len, 0.0,
                               gbs::tree_elim_top(S.n, lv, len) ? "tree_top_elim_kernel" : "tree_elim_kernel",
                               [&] { return gbs::launch_tree_elim(mp, sh, lv, g0 + q, len, st); }));
@@ -567,8 +570,8 @@ gbs::TreeShard tree_shard(int n, int shard, int nshards) {
         const uint64_t lo = cnt * (uint64_t)shard / (uint64_t)nshards, hi = cnt * (uint64_t)(shard + 1) / (uint64_t)nshards;
         if (lo >= hi) continue;  // lo = hi = 0: none
         // colex order of equal-size subsets is the order of their masks
-        sh.lo[s] = colex_mask(lo, n, s);
-        sh.hi[s] = hi == cnt ? 1ull << n : colex_mask(hi, n, s);
+        sh.lo[s] = (uint32_t)colex_mask(lo, n, s);
+        sh.hi[s] = (uint32_t)(hi == cnt ? 1ull << n : colex_mask(hi, n, s));
     }
     return sh;
 }
@@ -613,7 +616,6 @@ double tree_shard_share(const gbs::TreeShard& sh, int n) {
 
 // Subset sum on the subset tree: matrix A (device, N x N); shard g of G and
 // record_dev as for run_sum.
-constexpr size_t kTreeBudget = (size_t)4 << 30;  // entry stores of a single evaluation
 gbs_status run_sum_tree(DevCtx* c, const double2* A, int N, hipStream_t st, double2* out_dev, double* abs_dev,
                         int* launches, int shard, int nshards, double* record_dev) {
     const int n = (N + 1) / 2;
@@ -664,7 +666,7 @@ gbs_status run_sum_tree_dd(DevCtx* c, const double2* A, int N, hipStream_t st, d
     gbs::TreeMap mp{};
     mp.arena = static_cast<double2*>(c->E);
     mp.n = n;
-    for (int lv = 0; lv <= n; ++lv) mp.off[lv] = S.off[lv] * (uint64_t)(n + 1);
+    for (int lv = 0; lv <= n; ++lv) mp.off[lv] = (uint32_t)(S.off[lv] * (uint64_t)(n + 1));
     HIP_TRY(gbs::launch_tree_dd_root(mp, A, N, st));
     int nl = 1;
     uint64_t poff = 0;
@@ -682,7 +684,7 @@ gbs_status run_sum_tree_dd(DevCtx* c, const double2* A, int N, hipStream_t st, d
         }
         for (uint64_t q = 0; q < count; q += S.piece[lv]) {
             const uint64_t len = std::min(S.piece[lv], count - q);
-            mp.win[lv + 1] = g0 + q;
+            mp.win[lv + 1] = (uint32_t)(g0 + q);
             HIP_TRY(timed_launch(
                 kProfCharpoly, tree_flops(n, tree_child_products(n - lv - 1)) * (double)len, 0.0, st,
                 [&] { return gbs::launch_tree_dd_elim(mp, lv, g0 + q, len, st); },

@@ -18,14 +18,18 @@ constexpr int kTreeMaxPairs = 28;
 struct TreeMap {
     double2* arena;
     int n;
-    uint64_t off[kMaxPairs + 1];
-    uint64_t win[kMaxPairs + 1];
+    uint32_t off[kTreeMaxPairs + 1];
+    uint32_t win[kTreeMaxPairs + 1];
 };
 // Subsets of size s that are summed: masks lo[s] <= mask < hi[s] (all when !on).
 struct TreeShard {
     int on;
-    uint64_t lo[kMaxPairs + 1], hi[kMaxPairs + 1];
+    uint32_t lo[kTreeMaxPairs + 1], hi[kTreeMaxPairs + 1];
 };
+// A captured graph holds a copy per launch, and the no-allocation entry point
+// takes 14000 launches at N = 50: 32 bits are enough for stores of 4 GiB and masks
+// of kTreeMaxPairs bits.
+static_assert(kTreeMaxPairs < 32 && sizeof(TreeMap) + sizeof(TreeShard) <= 512, "kernel arguments");
 // Matrices of a forest: root r is item i = list[r] of packed matrices, dims[i] x
 // dims[i] row-major at mats + in_off[i], or (list null) the one N x N matrix
 // mats.  2n - 1 <= dimension <= 2n.
