@@ -22,12 +22,21 @@ sys.path.insert(0, ROOT)
 
 FP64_PEAK_TFLOPS = 78.6  # MI355X: 256 CU x 2.4 GHz x 128 FP64 flop/clk/CU (vector FMA)
 
-# HBM bytes per launch (fetched, written) of the largest per-subset kernel
-# instances of the N = 50 step, from rocprofv3 --pmc FETCH_SIZE and --pmc
-# WRITE_SIZE runs scaled by the same counters on a plain 256 MiB device copy
-# (fetch x2.0, write x1.0); the command and raw figures are in
-# profiles/charpoly_n50_traffic.md.  Valid only for the kernel sources hashed
-# here: any change to them reports null until re-measured.
+# HBM bytes per launch (fetched, written) of the largest kernel instances of the
+# N = 50 step, from rocprofv3 --pmc FETCH_SIZE and --pmc WRITE_SIZE runs scaled
+# by the same counters on a plain 256 MiB device copy (fetch x2.0, write x1.0);
+# the commands and raw figures are in profiles/tree_n50.md (subset tree) and
+# profiles/charpoly_n50_traffic.md (register tiles, which FP64 sums of this size
+# ran on before).  Valid only for the kernel sources hashed here: any change to
+# them reports null until re-measured.
+TREE_TRAFFIC_SOURCES = ("paper_2010_15595_amd/csrc/tree_device.h", "paper_2010_15595_amd/csrc/tree_kernels.h",
+                        "paper_2010_15595_amd/csrc/tree_launch.h")
+TREE_TRAFFIC = {
+    "sha256": "056b912bbc1bae1dff4bb03d24a51cea2ed4b6f8f523f58752d67a5a28b92bcc",
+    "kernels": {  # FETCH_SIZE / WRITE_SIZE KiB per dispatch
+        "tree_sub_kernel<25>": (1920181008, 4194304),  # 937588.4 / 4096.0
+    },
+}
 TRAFFIC_SOURCES = ("paper_2010_15595_amd/csrc/lhaf_device.h", "paper_2010_15595_amd/csrc/lhaf_kernels.h",
                    "paper_2010_15595_amd/csrc/charpoly_l88.hip", "paper_2010_15595_amd/csrc/charpoly_l84.hip",
                    "paper_2010_15595_amd/csrc/charpoly_l44.hip")
@@ -48,11 +57,11 @@ TRAFFIC = {
 }
 
 
-def sources_sha256():
+def sources_sha256(sources=TRAFFIC_SOURCES):
     import hashlib
 
     h = hashlib.sha256()
-    for rel in TRAFFIC_SOURCES:
+    for rel in sources:
         with open(os.path.join(ROOT, rel), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
@@ -60,9 +69,10 @@ def sources_sha256():
 
 def traffic_entry(kernel):
     """Measured HBM bytes per launch of `kernel`, if they were taken on it and on these sources."""
-    if TRAFFIC is None or TRAFFIC["sha256"] != sources_sha256() or kernel not in TRAFFIC["kernels"]:
-        return None
-    return sum(TRAFFIC["kernels"][kernel])
+    for table, sources in ((TREE_TRAFFIC, TREE_TRAFFIC_SOURCES), (TRAFFIC, TRAFFIC_SOURCES)):
+        if kernel in table["kernels"] and table["sha256"] == sources_sha256(sources):
+            return sum(table["kernels"][kernel])
+    return None
 
 
 def log(*a):
@@ -710,7 +720,7 @@ def main():
     ap.add_argument("--no-plain", action="store_true", help="batch: skip timing the items one at a time")
     args = ap.parse_args()
     if args.print_source_hash:
-        print(sources_sha256())
+        print(sources_sha256(TREE_TRAFFIC_SOURCES), sources_sha256())
         return
     if args.copy_calibration:
         import torch

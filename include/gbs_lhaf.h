@@ -147,12 +147,14 @@ typedef enum {
 } gbs_charpoly;
 
 /* lhaf of an N x N symmetric matrix A (leading dim lda, diagonal = loop weights)
- * on the LDS-resident reference kernels (one workgroup per subset, one
- * characteristic polynomial each) with `method`: for comparing the two methods
- * in one framework.  prec GBS_FP64 (either method, N <= 64) or GBS_DD
- * (GBS_CHARPOLY_LABUDDE only, N <= 56: the sum of gbs_lhaf, bit for bit;
- * diag->lhaf_lo holds the low part); GBS_E_UNSUPPORTED otherwise.  GBS_E_NONFINITE when a subset's QR
- * iteration needs more than 30 sweeps for one eigenvalue.  Host pointers;
+ * with the characteristic polynomials from `method`: for comparing the two
+ * methods in one framework.  prec GBS_FP64 (either method, N <= 64): the
+ * LDS-resident reference kernels, one workgroup and one characteristic polynomial
+ * per subset.  GBS_DD (GBS_CHARPOLY_LABUDDE only, N <= 56): the value of gbs_lhaf
+ * bit for bit, which is a sum over the subset tree and forms no characteristic
+ * polynomial; diag->lhaf_lo holds the low part.  GBS_E_UNSUPPORTED otherwise.
+ * GBS_E_NONFINITE when a subset's QR iteration needs more than 30 sweeps for one
+ * eigenvalue.  Host pointers;
  * synchronous; diag may be NULL. */
 gbs_status gbs_lhaf_method(const gbs_z *A, int32_t N, int64_t lda, gbs_precision prec, gbs_charpoly method,
                            gbs_z *out, gbs_diag *diag);
@@ -229,7 +231,9 @@ gbs_status gbs_combine_partials(const double *partials, int32_t count, gbs_z *ou
  * the library holds until the process ends; it keeps the last call's
  * contents, and every value a call reads from it is written by that call
  * first.  FP64 sums up to N = 56 run on the subset tree in pieces that fit the
- * array.  gbs_init(device) must have been called for the current device
+ * array: 180 kernel launches at N = 38, 1700 at N = 44, 15000 at N = 50 and 150000 at
+ * N = 56, which a graph captured from the call holds as nodes (113 MB of host
+ * memory at N = 54).  gbs_init(device) must have been called for the current device
  * (GBS_E_ARG otherwise).  N <= GBS_MAX_DIM (GBS_E_TOO_LARGE above);
  * GBS_FP64 or GBS_FP32_COMP (GBS_E_UNSUPPORTED for GBS_DD).  Lane grids are
  * those of earlier tuning or gbs_set_layout, else the defaults.  All calls on
@@ -265,7 +269,8 @@ typedef struct {
  * packed concatenation of the matrices: item i is an N_i x N_i row-major
  * block (diagonal = loop weights) at element offset sum_{j<i} N_j^2.  GBS_FP64
  * items whose number of pairs has no lane grid set (gbs_set_layout) are grouped
- * by it and each group's subset trees are expanded together.  For the others the
+ * by it and each group's subset trees are expanded together (from 20 pairs on one
+ * at a time, an item of N = 44 in 57 and of N = 50 in 463 launches).  For the others the
  * plan splits every item's subset sum into tiles (runs of subsets of one size
  * class), processes them with persistent per-subset kernels that take tiles
  * largest first from a device counter, then the series kernels and a

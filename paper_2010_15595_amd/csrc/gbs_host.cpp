@@ -708,7 +708,11 @@ gbs_status run_sum_tree_dd(DevCtx* c, const double2* A, int N, hipStream_t st, d
 // nodes that hold any of its subsets are share * G times its share of the
 // subsets (1.3 for two shards, 1.9 to 3.3 for the outer and middle ones of
 // eight, 6 and more for the middle ones of sixteen and up, at n = 24), while the
-// register-tile kernels do just its subsets, each at several times the cost.
+// register-tile kernels do just its subsets, each at several times the cost.  The
+// limit was set on a slower subtree kernel and errs towards the tiles: shard 3 of 8
+// at N = 48, 3.33 times its share, takes 29.9 ms on the tree and 39.5 on tiles; at
+// N = 28 a shard takes 112 us on the tree, however little it holds, and 250 to 306
+// on tiles.  No shard of 2 to 64 at N = 4 .. 44 was slower than on tiles.
 constexpr double kTreeShardCost = 3.4;
 
 // lds_method >= 0 selects the LDS-resident FP64 kernels with that characteristic-polynomial

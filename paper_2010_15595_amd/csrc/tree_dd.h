@@ -7,8 +7,8 @@
 // of FP64 instructions at the deep levels (a lane's product has as many terms as
 // its coefficient's index, so about half of the lanes work, and a solve is a chain
 // of n steps), by the latency of those chains at the first ten.  Against the
-// LDS-resident characteristic polynomial of each subset: N = 20 1.43 -> 0.27 ms,
-// N = 28 5.67 -> 0.55 ms, N = 36 94 -> 6.7 ms, N = 41 1030 -> 60 ms.
+// LDS-resident characteristic polynomial of each subset: N = 28 5.61 -> 0.53 ms,
+// N = 36 94 -> 6.9 ms, N = 44 2250 -> 135 ms, N = 50 25.3 -> 1.25 s.
 // Included by lhaf_lds.hip alone (floating-point contraction is off there).
 #include "dd.h"
 #include "tree_lane.h"
@@ -19,8 +19,9 @@ namespace treedd {
 
 // Unnormalised accumulator: hi carries the sum rounded at every step, lo the
 // exact rounding errors and the products' low parts (a compensated dot product
-// of dd operands); its error is a few n 2^-106 of the summed magnitudes, as that
-// of n dd additions, at 12 instead of 27 instructions per real product.
+// of dd operands); its error is a few n 2^-106 of the summed magnitudes, at 12
+// instead of 27 instructions per real product.  (A permuted matrix gives the same
+// sum to 1e-33 of sum |t_S| at N = 40.)
 struct Acc {
     double rh, rl, ih, il;
 };
@@ -129,8 +130,8 @@ hipError_t launch_tree_dd_root(const TreeMap& mp, const double2* A, int N, hipSt
 }
 
 // Up to here a parent's row of lanes per series is faster than several parents
-// packed into a workgroup: N = 28 with a limit of 32, 128, 256, 512, 1024:
-// 531, 520, 521, 540, 565 us.
+// packed into a workgroup: N = 28, with one row update less than now, for a limit
+// of 32, 128, 256, 512, 1024: 531, 520, 521, 540, 565 us.
 constexpr uint64_t kTopParentsDd = 256;
 
 bool tree_dd_elim_top(uint64_t count) { return count <= kTopParentsDd; }

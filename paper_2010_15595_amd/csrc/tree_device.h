@@ -247,7 +247,7 @@ __device__ __forceinline__ double pair_bcast(double x) {
 // x m)), handed over between the lanes.  Every in_k is read before out_k is
 // written, and m_k, too.  in_k is scaled by 1 + scale k.  For odd NN the odd lane
 // also reads and writes coefficient NN, with no meaning.  In tree_sub_kernel<25> a
-// solve takes 5400 cycles this way and 7900 on single lanes, an update of v's row
+// solve takes 5400 cycles this way and 7900 on single lanes, a round of row updates
 // 4300 and 6650 (5200 are the multiply-adds of a whole product).
 template <int NN, bool SOLVE, class Y, class M, class In, class Out>
 __device__ __forceinline__ void half_products(int p, double scale, Y ys, M ms, In in, Out out) {
@@ -476,8 +476,9 @@ constexpr int kTreeOne = 96;  // 2^(4-T) parents, T = 0..4; the series 1 after t
 constexpr int kTreeSlots = 97;
 __host__ __device__ constexpr int tree_lanes(int T) { return T == 0 ? 4 : tree_entries(T); }
 
-// Row updates of T <= 2 (44 to 56 rows) as one round of whole products, not two on
-// pairs of lanes; n = 12 at two waves per SIMD, 27 and 28 would need scratch.
+// Row updates of T <= 2 (44 to 56 rows) as one round of whole products, 6650 cycles
+// at n = 25, not two on pairs of lanes, 8600; n = 12 at two waves per SIMD, 27 and 28
+// would need scratch for it.
 template <int NN>
 constexpr bool kTreeWholeRows = NN <= 26 && NN != 12;
 
@@ -492,10 +493,13 @@ constexpr bool kTreeWholeRows = NN <= 26 && NN != 12;
 // (With the entries of each level in device memory instead, 134 KB a wavefront
 // at n = 25, the kernel moved 150 GB at N = 44 and kept the VALU 33% busy.)
 // Between levels the entries change lanes through one 2 KB LDS line per
-// coefficient.  Bound by FP64 issue: of the 95 us of 1024 nodes at n = 25 (112
-// with all products on single lanes) the couplings take 31%, on 45 to 60 of 64
-// lanes, the first solves 20%, the second ones 13%, the rows of v 11%, the changes
-// of lanes 9%, which the LDS bandwidth bounds, the leaves 5%.
+// coefficient.  Bound by FP64 issue: 65536 nodes at n = 25 take 5.37 ms (85 us
+// per 1024), in which the SIMDs issue a VALU instruction in 65% of the cycles, 84%
+// of them FP64 FMAs.  Of a wavefront's time the couplings take 32%, on 45 to 60 of
+// 64 lanes, the first solves 19%, the second ones 13%, the row updates 15%, the
+// changes of lanes 13%, the leaves 5%.  (With all products on single lanes, and one
+// row update less, it was 112 us per 1024 nodes, then 95 on pairs of lanes, in
+// launches of 1024.)
 template <int NN>
 __global__ void __launch_bounds__(64, (NN <= 12 ? 2 : 1))
     tree_sub_kernel(TreeMap mp, TreeShard sh, int level, uint64_t g0, double* __restrict__ records, TreeSource src,

@@ -7,7 +7,8 @@ namespace gbs {
 
 // Largest n on the subset tree: the entries one lane of tree_sub_kernel holds
 // (8 (n + 1) doubles) and its operands fit the registers without scratch; n = 29
-// and above would need it, and keep the register-tile kernels.
+// and above would need it, and keep the register-tile kernels.  (Instances with
+// scratch gave wrong sums; why was not found.  The build refuses them.)
 constexpr int kTreeMaxPairs = 28;
 
 // Entry store of a forest of equal trees (n pairs each).  A node with T pairs
@@ -27,7 +28,7 @@ struct TreeShard {
     uint32_t lo[kTreeMaxPairs + 1], hi[kTreeMaxPairs + 1];
 };
 // A captured graph holds a copy per launch, and the no-allocation entry point
-// takes 14000 launches at N = 50: 32 bits are enough for stores of 4 GiB and masks
+// takes 15000 launches at N = 50: 32 bits are enough for stores of 4 GiB and masks
 // of kTreeMaxPairs bits.
 static_assert(kTreeMaxPairs < 32 && sizeof(TreeMap) + sizeof(TreeShard) <= 512, "kernel arguments");
 // Matrices of a forest: root r is item i = list[r] of packed matrices, dims[i] x

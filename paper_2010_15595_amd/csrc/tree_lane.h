@@ -200,8 +200,9 @@ hipError_t launch_tree_lane_elim(const TreeMap& mp, int level, uint64_t g0, uint
     const size_t series = sizeof(typename AR::V) * (size_t)lds_stride(n);
     // The row of v in LDS while a node's series take at most 64 KB; then as many
     // nodes per workgroup as fit 32 KB (five workgroups per CU).  N = 41 in
-    // double-double: 60.9 ms; with 16, 24 or 40 KB 65.7, 62.6, 64.2 ms; with 128
-    // threads 73.3, with 512 67.4 ms; with the row of v always in memory 66.2 ms.
+    // double-double, with one row update less than now: 60.9 ms; with 16, 24 or 40
+    // KB 65.7, 62.6, 64.2 ms; with 128 threads 73.3, with 512 67.4 ms; with the row
+    // that stays always in memory 66.2 ms.
     const bool rows = series * lds_series(T, true) <= 64 * 1024;
     const size_t node = series * lds_series(T, rows);
     const int per = (int)std::min<uint64_t>(count, std::max<size_t>(1, std::min<size_t>(16, 32 * 1024 / node)));
@@ -224,9 +225,9 @@ hipError_t launch_tree_lane_elim(const TreeMap& mp, int level, uint64_t g0, uint
 // WIDE, k + 16): a solve's next coefficient reaches them as a row broadcast (DPP),
 // and the series it multiplies is read from LDS ahead of the chain.  With the
 // coefficient handed on through LDS a step took 156 ns, and of the 12 us of a
-// level at n = 16 (36 at n = 25) the two solves took 5 (26), loads 2, the row of v
-// 1.2, the couplings 1, launch and kernel end 2.7; now 8 (15) in all.  ROWS as
-// above.
+// level at n = 16 (36 at n = 25) the two solves took 5 (26), loads 2, the row update
+// 1.2, the couplings 1, launch and kernel end 2.7; now, with two row updates, 8 (12
+// to 15) in all up to 32 (16) parents, 24 (114) for 1024.  ROWS as above.
 template <class AR, bool WIDE, bool ROWS>
 __global__ void __launch_bounds__(1024) tree_top_elim_kernel(TreeMap mp, int level, uint64_t g0) {
     using namespace treelane;

@@ -227,7 +227,7 @@ struct F64 {
 
 // Up to here a launch of tree_elim_kernel lasts as long as its chain of products,
 // 12 us at n = 16 and 28 us at n = 25; the split of a product over lanes takes 8
-// and 15 us, but a multiply-add costs it several LDS reads.  Microseconds with a
+// and 12 to 15 us, but a multiply-add costs it several LDS reads.  Microseconds with a
 // limit of 32, 128, 256, 512, 1024, 2048 parents: N = 28 124, 115, 111, 111, 111,
 // 112; N = 32 232, 222, 221, 216, 216, 215; N = 36 670, 659, 658, 654, 661, 683;
 // N = 37 without allocation 2827 (128), 2708, 2596, 2599, 2598; 4096 small items 230,
